@@ -456,22 +456,24 @@ __global__ __launch_bounds__(256) void k_attn_partial_px(AttnArgs a) {
   }
 }
 
-// out[slot][h*hd + dim] = sum_s o_s 2^(m_s - m) / sum_s l_s 2^(m_s - m).
-// grid (H, HD / 32, slot halves), block 256: thread -> (slot, 4 consecutive dims).
+// out[slot][h*hd + dim] = sum_s o_s 2^(m_s - m) / sum_s l_s 2^(m_s - m), as
+// tiled activations. grid (H, HD / 64, slots / 8), one wave: lane -> (slot, 8
+// consecutive dims), so that a wave reads 256 contiguous bytes of each slot's
+// partial and writes whole 128-byte lines of the tile.
 // The partials were written by workgroups on every XCD (far-memory round
 // trips), so the splits are taken in groups of kCombGroup whose loads are all
 // in flight at once; groups are merged with a running maximum.
 constexpr int kCombGroup = 16;
 template <int HD>
-__global__ __launch_bounds__(256) void k_attn_combine(AttnArgs a) {
-  const int h = blockIdx.x, t = threadIdx.x;
-  const int slot = blockIdx.z * 32 + (t >> 3), dim0 = blockIdx.y * 32 + (t & 7) * 4;
+__global__ __launch_bounds__(64) void k_attn_combine(AttnArgs a) {
+  const int h = blockIdx.x, lane = threadIdx.x;
+  const int slot = blockIdx.z * 8 + (lane >> 3), dim0 = blockIdx.y * 64 + (lane & 7) * 8;
   if (slot >= a.M) return;
-  const size_t oo = (size_t)slot * a.ldo + (size_t)h * HD + dim0;
+  uint16_t* out = a.out + act_off(slot, h * HD + dim0, a.mtiles);
   const bool two = a.st.mode != kStreamsOne;
   if (two && (slot & 31) >= a.st.L) {  // padding row of a multi-stream window: finite zeros
-    *(ushort4*)(a.out + oo) = make_ushort4(0, 0, 0, 0);
-    *(ushort4*)(a.out_lo + oo) = make_ushort4(0, 0, 0, 0);
+    *(uint4*)out = make_uint4(0, 0, 0, 0);
+    *(uint4*)(out + kActLo) = make_uint4(0, 0, 0, 0);
     return;
   }
   const int n = stream_rows(a.st, a.n_dev ? *a.n_dev : a.n_host, slot >> 5);
@@ -480,15 +482,16 @@ __global__ __launch_bounds__(256) void k_attn_combine(AttnArgs a) {
   const float* wml = a.ws_ml + (size_t)h * a.nsplit_max * kWinRows * 2 + slot * 2;
   const float* wo = a.ws_o + ((size_t)h * a.nsplit_max * kWinRows + slot) * HD + dim0;
   float mx = -INFINITY, ls = 0.0f;
-  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+  float acc[8] = {};
   for (int s0 = 0; s0 < ns; s0 += kCombGroup) {
     float2 ml[kCombGroup];
-    float4 v[kCombGroup];
+    float4 v[kCombGroup], u[kCombGroup];
 #pragma unroll
     for (int i = 0; i < kCombGroup; ++i) {
       const int sx = s0 + i < ns ? s0 + i : ns - 1;
       ml[i] = *(const float2*)(wml + (size_t)sx * kWinRows * 2);
       v[i] = *(const float4*)(wo + (size_t)sx * kWinRows * HD);
+      u[i] = *(const float4*)(wo + (size_t)sx * kWinRows * HD + 4);
     }
     float gm = mx;
 #pragma unroll
@@ -497,10 +500,8 @@ __global__ __launch_bounds__(256) void k_attn_combine(AttnArgs a) {
     if (gm != mx && mx != -INFINITY) {  // rescale what the earlier groups summed
       const float r = exp2f(mx - gm);
       ls *= r;
-      acc.x *= r;
-      acc.y *= r;
-      acc.z *= r;
-      acc.w *= r;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) acc[e] *= r;
     }
     mx = gm;
 #pragma unroll
@@ -508,25 +509,26 @@ __global__ __launch_bounds__(256) void k_attn_combine(AttnArgs a) {
       if (s0 + i < ns) {
         const float f = ml[i].x == -INFINITY ? 0.0f : exp2f(ml[i].x - mx);
         ls += ml[i].y * f;
-        acc.x += v[i].x * f;
-        acc.y += v[i].y * f;
-        acc.z += v[i].z * f;
-        acc.w += v[i].w * f;
+        acc[0] += v[i].x * f;
+        acc[1] += v[i].y * f;
+        acc[2] += v[i].z * f;
+        acc[3] += v[i].w * f;
+        acc[4] += u[i].x * f;
+        acc[5] += u[i].y * f;
+        acc[6] += u[i].z * f;
+        acc[7] += u[i].w * f;
       }
   }
-  ushort4 hi, lo;
-  split_bf16(acc.x / ls, hi.x, lo.x);
-  split_bf16(acc.y / ls, hi.y, lo.y);
-  split_bf16(acc.z / ls, hi.z, lo.z);
-  split_bf16(acc.w / ls, hi.w, lo.w);
-  *(ushort4*)(a.out + oo) = hi;
-  *(ushort4*)(a.out_lo + oo) = lo;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) acc[e] /= ls;
+  store_act<8>(out, acc);
 }
 
 hipError_t launch_attention(const AttnArgs& a, int hd, hipStream_t s) {
+  if (a.M > 32 * a.mtiles) return hipErrorInvalidValue;
   if (a.M < 1 || a.M > (a.st.mode == kStreamsOne ? 64 : 32 * kMaxStreams)) return hipErrorInvalidValue;
   const unsigned zh = (unsigned)(a.M + 31) / 32;  // 32-slot blocks
-  const dim3 g1(a.H, a.nsplit_max, zh), g2(a.H, hd / 32, zh);
+  const dim3 g1(a.H, a.nsplit_max, zh), g2(a.H, hd / 64, (unsigned)(a.M + 7) / 8);
   if (hd == 128) {
     // one workgroup per key / value head: its tiles are read once for the
     // whole group of query heads that share them
@@ -535,10 +537,10 @@ hipError_t launch_attention(const AttnArgs& a, int hd, hipStream_t s) {
     const dim3 gp((unsigned)(a.Hkv * a.qparts), a.nsplit_max, zh);
     if (G / a.qparts > 1) hipLaunchKernelGGL(k_attn_partial_px<true>, gp, dim3(256), 0, s, a);
     else hipLaunchKernelGGL(k_attn_partial_px<false>, gp, dim3(256), 0, s, a);
-    hipLaunchKernelGGL(k_attn_combine<128>, g2, dim3(256), 0, s, a);
+    hipLaunchKernelGGL(k_attn_combine<128>, g2, dim3(64), 0, s, a);
   } else if (hd == 64) {
     hipLaunchKernelGGL(k_attn_partial<64>, g1, dim3(256), 0, s, a);
-    hipLaunchKernelGGL(k_attn_combine<64>, g2, dim3(256), 0, s, a);
+    hipLaunchKernelGGL(k_attn_combine<64>, g2, dim3(64), 0, s, a);
   } else {
     return hipErrorInvalidValue;
   }

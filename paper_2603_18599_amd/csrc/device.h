@@ -71,6 +71,31 @@ SJD_DEV void split_bf16(float v, uint16_t& hi, uint16_t& lo) {
   lo = f32_to_bf16(v - bf16_to_f32(hi));
 }
 
+// C (4 or 8) consecutive columns of one activation row as hi / lo bf16: the hi
+// plane of their tile at y, the lo plane kActLo elements on (forward.h's
+// activation tiles)
+constexpr int kActLo = 2048;
+template <int C>
+SJD_DEV void store_act(uint16_t* y, const float (&v)[C]) {
+  static_assert(C == 4 || C == 8, "half a 16-byte chunk or a whole one");
+  uint32_t h[C / 2], l[C / 2];
+#pragma unroll
+  for (int e = 0; e < C; e += 2) {
+    uint16_t h0, l0, h1, l1;
+    split_bf16(v[e], h0, l0);
+    split_bf16(v[e + 1], h1, l1);
+    h[e / 2] = (uint32_t)h0 | ((uint32_t)h1 << 16);
+    l[e / 2] = (uint32_t)l0 | ((uint32_t)l1 << 16);
+  }
+  if constexpr (C == 8) {
+    *(uint4*)y = make_uint4(h[0], h[1], h[2], h[3]);
+    *(uint4*)(y + kActLo) = make_uint4(l[0], l[1], l[2], l[3]);
+  } else {
+    *(uint2*)y = make_uint2(h[0], h[1]);
+    *(uint2*)(y + kActLo) = make_uint2(l[0], l[1]);
+  }
+}
+
 // split_bf16 for values known to be finite (no NaN / Inf handling)
 SJD_DEV void split_bf16_finite(float v, uint16_t& hi, uint16_t& lo) {
   const uint32_t u = __float_as_uint(v);

@@ -37,15 +37,16 @@ struct Ctx {
   const uint16_t* fnorm = nullptr;
   const uint16_t* head = nullptr;
   std::vector<std::array<const uint16_t*, 9>> lw;
-  int ld_d = 0, ld_q = 0, ld_f = 0;  // padded row strides of the activation planes
   std::vector<void*> owned;
-  // activations entering MFMAs are hi / lo bf16 plane pairs
+  // activations entering GEMMs are tiled hi / lo bf16 planes (forward.h); q is
+  // row-major, hi and lo planes
+  int mtiles = 2;  // Mpad / 32
   float* x = nullptr;
-  uint16_t *xn = nullptr, *xn_lo = nullptr;
+  uint16_t* xn = nullptr;
   float* qkv = nullptr;
   uint16_t *q = nullptr, *q_lo = nullptr;
-  uint16_t *att = nullptr, *att_lo = nullptr;
-  uint16_t *hbuf = nullptr, *hbuf_lo = nullptr;
+  uint16_t* att = nullptr;
+  uint16_t* hbuf = nullptr;
   uint16_t *kc = nullptr, *kc_lo = nullptr;
   uint16_t *vt = nullptr, *vt_lo = nullptr;
   // streams: one per image of a batch (up to four), two per image for a
@@ -176,9 +177,9 @@ int forward(Ctx& x, int M, const int32_t* n_dev, int n_host, float* logits, cons
     const auto& w = x.lw[l];
     const size_t lofs = (size_t)l * Hkv * x.cap_pad * hd + (size_t)cache * x.kv_elems;
     sjd::KvPlanes kv{x.q, x.q_lo, x.kc + lofs, x.kc_lo + lofs, x.vt + lofs, x.vt_lo + lofs, x.kv_elems};
-    HIPTRY(sjd::launch_resid_norm(x.x, x.rpart, pend, rplane, w[0], M, d, x.xn, x.xn_lo, x.ld_d, x.ss, s));
+    HIPTRY(sjd::launch_resid_norm(x.x, x.rpart, pend, rplane, w[0], M, d, x.xn, x.mtiles, x.ss, s));
     sjd::GemmArgs g = normed;
-    g.A = x.xn; g.A_lo = x.xn_lo; g.lda = x.ld_d; g.M = M; g.W = w[1]; g.N = Nqkv; g.K = d; g.S = P[kProjQkv].S;
+    g.A = x.xn; g.mtiles = x.mtiles; g.M = M; g.W = w[1]; g.N = Nqkv; g.K = d; g.S = P[kProjQkv].S;
     g.wide = P[kProjQkv].wide; g.out = x.qkv; g.plane = qplane; g.ldo = Nqkv;
     HIPTRY(sjd::launch_gemm(g, s));
     HIPTRY(sjd::launch_rope_kv(x.qkv, P[kProjQkv].S, qplane, x.win, n_dev, n_host, M, H, Hkv, hd, x.rope, kv, x.cap_pad,
@@ -188,29 +189,29 @@ int forward(Ctx& x, int M, const int32_t* n_dev, int n_host, float* logits, cons
     a.sstride = kv.sstride; a.st = sm;
     a.n_dev = n_dev; a.n_host = n_host; a.M = M; a.H = H; a.Hkv = Hkv; a.cap = x.cap_pad;
     a.scale = (float)(1.4426950408889634 / std::sqrt((double)hd));
-    a.ws_o = x.attn_o; a.ws_ml = x.attn_ml; a.nsplit_max = x.nsplit_max; a.out = x.att; a.out_lo = x.att_lo;
-    a.ldo = x.ld_q; a.qparts = x.qparts;
+    a.ws_o = x.attn_o; a.ws_ml = x.attn_ml; a.nsplit_max = x.nsplit_max; a.out = x.att;
+    a.mtiles = x.mtiles; a.qparts = x.qparts;
     HIPTRY(sjd::launch_attention(a, hd, s));
     g = sjd::GemmArgs{};
-    g.A = x.att; g.A_lo = x.att_lo; g.lda = x.ld_q; g.M = M; g.W = w[4]; g.N = d; g.K = Nq; g.S = P[kProjO].S;
+    g.A = x.att; g.mtiles = x.mtiles; g.M = M; g.W = w[4]; g.N = d; g.K = Nq; g.S = P[kProjO].S;
     g.wide = P[kProjO].wide; g.out = x.rpart; g.plane = rplane; g.ldo = d;
     HIPTRY(sjd::launch_gemm(g, s));
-    HIPTRY(sjd::launch_resid_norm(x.x, x.rpart, P[kProjO].S, rplane, w[5], M, d, x.xn, x.xn_lo, x.ld_d, x.ss, s));
+    HIPTRY(sjd::launch_resid_norm(x.x, x.rpart, P[kProjO].S, rplane, w[5], M, d, x.xn, x.mtiles, x.ss, s));
     g = normed;
-    g.A = x.xn; g.A_lo = x.xn_lo; g.lda = x.ld_d; g.M = M; g.W = w[6]; g.N = 2 * F; g.K = d; g.S = P[kProjGu].S;
+    g.A = x.xn; g.mtiles = x.mtiles; g.M = M; g.W = w[6]; g.N = 2 * F; g.K = d; g.S = P[kProjGu].S;
     g.wide = P[kProjGu].wide; g.out = x.gup; g.plane = guplane; g.ldo = 2 * F;
     HIPTRY(sjd::launch_gemm(g, s));
-    HIPTRY(sjd::launch_swiglu(x.gup, P[kProjGu].S, guplane, M, F, x.hbuf, x.hbuf_lo, x.ld_f, s));
+    HIPTRY(sjd::launch_swiglu(x.gup, P[kProjGu].S, guplane, M, F, x.hbuf, x.mtiles, s));
     g = sjd::GemmArgs{};
-    g.A = x.hbuf; g.A_lo = x.hbuf_lo; g.lda = x.ld_f; g.M = M; g.W = w[8]; g.N = d; g.K = F; g.S = P[kProjDown].S;
+    g.A = x.hbuf; g.mtiles = x.mtiles; g.M = M; g.W = w[8]; g.N = d; g.K = F; g.S = P[kProjDown].S;
     g.wide = P[kProjDown].wide; g.out = x.rpart; g.plane = rplane; g.ldo = d;
     HIPTRY(sjd::launch_gemm(g, s));
     pend = P[kProjDown].S;
   }
   if (logits) {
-    HIPTRY(sjd::launch_resid_norm(x.x, x.rpart, pend, rplane, x.fnorm, M, d, x.xn, x.xn_lo, x.ld_d, x.ss, s));
+    HIPTRY(sjd::launch_resid_norm(x.x, x.rpart, pend, rplane, x.fnorm, M, d, x.xn, x.mtiles, x.ss, s));
     sjd::GemmArgs g = normed;
-    g.A = x.xn; g.A_lo = x.xn_lo; g.lda = x.ld_d; g.M = M; g.W = x.head; g.N = c.V; g.K = d; g.S = 1;
+    g.A = x.xn; g.mtiles = x.mtiles; g.M = M; g.W = x.head; g.N = c.V; g.K = d; g.S = 1;
     g.wide = 1;  // measured faster at 32 and 64 rows
     g.out = logits; g.plane = 0; g.ldo = c.V;
     if (sm.mode == sjd::kStreamsMulti && sm.guided) {  // rows [32 b, 32 b + L): image b's guided logits
@@ -309,7 +310,7 @@ Ctx::Plan tune_projection(Ctx& x, int proj, const std::vector<Ctx::Plan>& cand, 
     g.M = M; g.S = S; g.wide = pl.wide;
     if (proj == kProjQkv || proj == kProjGu) {
       g.ss = x.ss; g.ss_n = sjd::norm_chunks(d); g.inv_d = 1.0f / (float)d; g.eps = c.rms_eps;
-      g.A = x.xn; g.A_lo = x.xn_lo; g.lda = x.ld_d; g.K = d;
+      g.A = x.xn; g.mtiles = x.mtiles; g.K = d;
     }
     hipError_t e;
     switch (proj) {
@@ -320,19 +321,19 @@ Ctx::Plan tune_projection(Ctx& x, int proj, const std::vector<Ctx::Plan>& cand, 
         return sjd::launch_rope_kv(x.qkv, S, qplane, x.win, nullptr, 0, M, H, Hkv, hd, x.rope, kv, x.cap_pad, one, s);
       }
       case kProjO:
-        g.A = x.att; g.A_lo = x.att_lo; g.lda = x.ld_q; g.W = w[4]; g.N = d; g.K = Nq;
+        g.A = x.att; g.mtiles = x.mtiles; g.W = w[4]; g.N = d; g.K = Nq;
         g.out = x.rpart; g.plane = rplane; g.ldo = d;
         if ((e = sjd::launch_gemm(g, s)) != hipSuccess) return e;
-        return sjd::launch_resid_norm(x.x, x.rpart, S, rplane, w[5], M, d, x.xn, x.xn_lo, x.ld_d, x.ss, s);
+        return sjd::launch_resid_norm(x.x, x.rpart, S, rplane, w[5], M, d, x.xn, x.mtiles, x.ss, s);
       case kProjGu:
         g.W = w[6]; g.N = 2 * F; g.out = x.gup; g.plane = guplane; g.ldo = 2 * F;
         if ((e = sjd::launch_gemm(g, s)) != hipSuccess) return e;
-        return sjd::launch_swiglu(x.gup, S, guplane, M, F, x.hbuf, x.hbuf_lo, x.ld_f, s);
+        return sjd::launch_swiglu(x.gup, S, guplane, M, F, x.hbuf, x.mtiles, s);
       default:
-        g.A = x.hbuf; g.A_lo = x.hbuf_lo; g.lda = x.ld_f; g.W = w[8]; g.N = d; g.K = F;
+        g.A = x.hbuf; g.mtiles = x.mtiles; g.W = w[8]; g.N = d; g.K = F;
         g.out = x.rpart; g.plane = rplane; g.ldo = d;
         if ((e = sjd::launch_gemm(g, s)) != hipSuccess) return e;
-        return sjd::launch_resid_norm(x.x, x.rpart, S, rplane, w[0], M, d, x.xn, x.xn_lo, x.ld_d, x.ss, s);
+        return sjd::launch_resid_norm(x.x, x.rpart, S, rplane, w[0], M, d, x.xn, x.mtiles, x.ss, s);
     }
   };
   hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -424,6 +425,7 @@ extern "C" int sjd_init(const sjd_config* cfg, const sjd_weights* w, void* strea
   x.B = c.batch > 1 ? c.batch : 1;
   x.nstreams = x.B * (x.guided ? 2 : 1);
   x.Mpad = x.nstreams > 2 ? 32 * x.nstreams : 64;
+  x.mtiles = x.Mpad / 32;
   auto fail = [&](int rc) {
     sjd_destroy(h);
     return rc;
@@ -493,17 +495,12 @@ extern "C" int sjd_init(const sjd_config* cfg, const sjd_weights* w, void* strea
   const int Mp = x.Mpad;
   x.kv_elems = (size_t)c.n_layers * Hkv * x.cap_pad * hd;
   const size_t kv = x.kv_elems * x.nstreams;  // every stream's caches
-  // activation rows padded by 64 elements so that the 32 rows a wave reads per
-  // k-step spread over memory channels
-  x.ld_d = d + 64;
-  x.ld_q = Nq + 64;
-  x.ld_f = F + 64;
-  const size_t xnsz = (size_t)Mp * x.ld_d;
-  if ((rc = dalloc(x, &x.x, (size_t)Mp * d)) || (rc = dalloc(x, &x.xn, xnsz)) || (rc = dalloc(x, &x.xn_lo, xnsz)) ||
+  const size_t xnsz = sjd::act_elems(d, x.mtiles), attsz = sjd::act_elems(Nq, x.mtiles),
+               hsz = sjd::act_elems(F, x.mtiles);
+  if ((rc = dalloc(x, &x.x, (size_t)Mp * d)) || (rc = dalloc(x, &x.xn, xnsz)) ||
       (rc = dalloc(x, &x.q, (size_t)Mp * Nq)) ||
-      (rc = dalloc(x, &x.q_lo, (size_t)Mp * Nq)) || (rc = dalloc(x, &x.att, (size_t)Mp * x.ld_q)) ||
-      (rc = dalloc(x, &x.att_lo, (size_t)Mp * x.ld_q)) || (rc = dalloc(x, &x.hbuf, (size_t)Mp * x.ld_f)) ||
-      (rc = dalloc(x, &x.hbuf_lo, (size_t)Mp * x.ld_f)) || (rc = dalloc(x, &x.kc, kv)) || (rc = dalloc(x, &x.kc_lo, kv)) ||
+      (rc = dalloc(x, &x.q_lo, (size_t)Mp * Nq)) || (rc = dalloc(x, &x.att, attsz)) ||
+      (rc = dalloc(x, &x.hbuf, hsz)) || (rc = dalloc(x, &x.kc, kv)) || (rc = dalloc(x, &x.kc_lo, kv)) ||
       (rc = dalloc(x, &x.vt, kv)) || (rc = dalloc(x, &x.vt_lo, kv)) ||
       (rc = dalloc(x, &x.rope, (size_t)x.cap_pad * (hd / 2))) ||
       (rc = dalloc(x, &x.logits[0], (size_t)logit_rows(x) * c.V)) ||
@@ -617,14 +614,11 @@ extern "C" int sjd_init(const sjd_config* cfg, const sjd_weights* w, void* strea
   ok = ok && hipMemsetAsync(x.win, 0, sizeof(sjd::Window), s) == hipSuccess;
   ok = ok && hipMemsetAsync(x.x, 0, (size_t)Mp * d * sizeof(float), s) == hipSuccess;
   for (void* p : zero) ok = ok && hipMemsetAsync(p, 0, kv * 2, s) == hipSuccess;
-  void* zero2[] = {x.xn, x.xn_lo};
-  for (void* p : zero2) ok = ok && hipMemsetAsync(p, 0, xnsz * 2, s) == hipSuccess;
-  void* zero3[] = {x.att, x.att_lo};
-  for (void* p : zero3) ok = ok && hipMemsetAsync(p, 0, (size_t)Mp * x.ld_q * 2, s) == hipSuccess;
+  ok = ok && hipMemsetAsync(x.xn, 0, xnsz * 2, s) == hipSuccess;
+  ok = ok && hipMemsetAsync(x.att, 0, attsz * 2, s) == hipSuccess;
   void* zero5[] = {x.q, x.q_lo};
   for (void* p : zero5) ok = ok && hipMemsetAsync(p, 0, (size_t)Mp * Nq * 2, s) == hipSuccess;
-  void* zero4[] = {x.hbuf, x.hbuf_lo};
-  for (void* p : zero4) ok = ok && hipMemsetAsync(p, 0, (size_t)Mp * x.ld_f * 2, s) == hipSuccess;
+  ok = ok && hipMemsetAsync(x.hbuf, 0, hsz * 2, s) == hipSuccess;
   if (!ok) return fail(SJD_EHIP);
   // rotary table in double precision: rope[pos][i] = (cos, sin)(pos * theta^(-2i/hd))
   {
@@ -665,9 +659,9 @@ extern "C" int sjd_init(const sjd_config* cfg, const sjd_weights* w, void* strea
   if (tuned) {
     bool okz = hipMemsetAsync(x.x, 0, (size_t)Mp * d * sizeof(float), s) == hipSuccess;
     for (void* p : zero) okz = okz && hipMemsetAsync(p, 0, kv * 2, s) == hipSuccess;
-    for (void* p : zero2) okz = okz && hipMemsetAsync(p, 0, xnsz * 2, s) == hipSuccess;
+    okz = okz && hipMemsetAsync(x.xn, 0, xnsz * 2, s) == hipSuccess;
     for (void* p : zero5) okz = okz && hipMemsetAsync(p, 0, (size_t)Mp * Nq * 2, s) == hipSuccess;
-    for (void* p : zero4) okz = okz && hipMemsetAsync(p, 0, (size_t)Mp * x.ld_f * 2, s) == hipSuccess;
+    okz = okz && hipMemsetAsync(x.hbuf, 0, hsz * 2, s) == hipSuccess;
     if (!okz || hipStreamSynchronize(s) != hipSuccess) return fail(SJD_EHIP);
   }
   if (x.use_graph && hipStreamCreateWithFlags(&x.cap_stream, hipStreamNonBlocking) != hipSuccess)

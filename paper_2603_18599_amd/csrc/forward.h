@@ -16,10 +16,23 @@ constexpr int kGemmMaxSplits = 32;
 // per k-step instead of tiles a whole row block apart, which measurably
 // streams faster). Matrices that share an input (q, k, v; gate, up) are
 // tiled as row blocks of one [N][K].
+//
+// Activations that enter a GEMM are stored the same way: tile (kb, mt), rows
+// [32 mt, 32 mt + 32) x columns [64 kb, 64 kb + 64), holds its hi plane and then
+// its lo plane (kActLo = 2048 elements each, the order above), at element (kb * mtiles +
+// mt) * 4096 (mtiles = the buffer's row tiles). A wave stages 1 KB of it with
+// one contiguous load; from row-major planes the same load touched 64 separate
+// 16-byte pieces and kept the address unit busy four times as long, which at
+// 64 and 128 rows was what the GEMM waited for.
+__host__ __device__ inline size_t act_off(int m, int k, int mtiles) {
+  const int lane = (m & 31) + (k & 32), i = (k & 31) >> 3;
+  return ((size_t)(k >> 6) * mtiles + (m >> 5)) * 4096 + (size_t)(i * 64 + lane) * 8 + (k & 7);
+}
+inline size_t act_elems(int K, int mtiles) { return (size_t)(K / 64) * mtiles * 4096; }
+
 struct GemmArgs {
-  const uint16_t* A;     // activations as two bf16 planes (A = hi + lo), 32 rows
-  const uint16_t* A_lo;  // per started 32 (rows >= M finite), row stride lda
-  int lda;
+  const uint16_t* A;   // activations as two bf16 planes (A = hi + lo), tiled as
+  int mtiles;          // above (rows >= M of a started tile finite)
   int M;               // 1..128
   const uint16_t* W;   // tiled weights [N][K]
   int N, K;            // N multiple of 32, K multiple of 64
@@ -142,9 +155,8 @@ struct AttnArgs {
   float* ws_o;           // [H][nsplit_max][128][hd] partial outputs (per query slot)
   float* ws_ml;          // [H][nsplit_max][128][2]  partial max (log2 domain) and sum
   int nsplit_max;
-  uint16_t* out;         // [Mpad][ldo]
-  uint16_t* out_lo;
-  int ldo;
+  uint16_t* out;         // tiled activations (act_off), `mtiles` row tiles
+  int mtiles;
   int qparts;            // workgroups per key / value head, each taking H / Hkv / qparts query heads
 };
 constexpr int kAttnChunk = 128;  // keys per workgroup (4 waves x 32)
@@ -155,12 +167,12 @@ hipError_t launch_attention(const AttnArgs& a, int hd, hipStream_t s);
 hipError_t launch_embed(const uint16_t* E, const Window* win, int M, int d, int vocab, int fallback, float* x,
                         hipStream_t s);
 // RMSNorm split in two: x += sum of S fp32 partial planes (fixed order; S
-// may be 0), y = x * g as hi / lo bf16 planes (row stride ldy) and the
-// sums of squares of x over 256-element chunks, ss[m][c] (c < norm_chunks(d));
-// the GEMM that consumes y applies the row scale 1 / sqrt(mean(x^2) + eps).
+// may be 0), y = x * g as tiled activations (mtiles row tiles) and the sums of
+// squares of x over 256-element chunks, ss[m][c] (c < norm_chunks(d)); the GEMM
+// that consumes y applies the row scale 1 / sqrt(mean(x^2) + eps).
 inline int norm_chunks(int d) { return (d + 255) / 256; }
 hipError_t launch_resid_norm(float* x, const float* part, int S, size_t plane, const uint16_t* g, int M, int d,
-                             uint16_t* y, uint16_t* y_lo, int ldy, float* ss, hipStream_t s);
+                             uint16_t* y, int mtiles, float* ss, hipStream_t s);
 // rotary embedding of q and k, key row and transposed value column into the caches
 struct KvPlanes {
   uint16_t *q, *q_lo, *kc, *kc_lo, *vt, *vt_lo;
@@ -170,11 +182,9 @@ struct KvPlanes {
 hipError_t launch_rope_kv(const float* qkv, int S, size_t plane, const Window* win, const int32_t* n_dev, int n_host,
                           int M, int H, int Hkv, int hd, const float2* rope, const KvPlanes& o, int cap,
                           const Streams& st, hipStream_t s);
-// h = silu(gate) * up as hi / lo bf16 planes (row stride ldh), gate = sum of
-// the S fp32 partial planes at columns [0, F), up = at columns [F, 2F)
-// (row stride 2F)
-hipError_t launch_swiglu(const float* P, int S, size_t plane, int M, int F, uint16_t* h, uint16_t* h_lo, int ldh,
-                         hipStream_t s);
+// h = silu(gate) * up as tiled activations, gate = sum of the S fp32 partial
+// planes at columns [0, F), up = at columns [F, 2F) (row stride 2F)
+hipError_t launch_swiglu(const float* P, int S, size_t plane, int M, int F, uint16_t* h, int mtiles, hipStream_t s);
 hipError_t launch_f32_to_bf16(const float* src, uint16_t* dst, size_t n, hipStream_t s);
 
 }  // namespace sjd

@@ -16,6 +16,11 @@
 //    column blocks per workgroup halve the activation loads per weight byte
 //    again, which 64-row windows need most (their QKV, gate/up and LM-head
 //    GEMMs ran 17-27% faster);
+//  - the activation tiles are stored in the order the workgroup stages them
+//    (forward.h), so each of its loads is 1 KB of consecutive bytes. 7B shapes,
+//    in the engine, row-major planes -> tiles: 128 rows QKV 46.2 -> 33.5 us,
+//    gate/up 83.2 -> 57.6, LM head 160 -> 132; 64 rows QKV 24.7 -> 23.2, gate/up
+//    43.9 -> 38.8; 32 rows within 1 us (the weight stream hides the loads);
 //  - the contraction index is permuted identically in A and W (any
 //    permutation of k leaves the sum unchanged), so both operands load as
 //    16-byte chunks straight into the MFMA register layout;
@@ -52,7 +57,9 @@ SJD_DEV bf16x8 as_bf16x8(const u32x4& u) { return __builtin_bit_cast(bf16x8, u);
 
 template <int MT>
 struct GemmSmem {
-  u32x4 a[2][2][MT][4][kWave];  // [buffer][hi / lo][row tile][16-byte chunk][lane]: A tiles in MFMA operand order
+  // [buffer][row tile][hi / lo][16-byte chunk][lane]: A tiles in MFMA operand
+  // order, as in memory
+  u32x4 a[2][MT][2][4][kWave];
   float inv[32 * MT];
 };
 
@@ -107,22 +114,14 @@ __global__ __launch_bounds__(NW * kWave) void k_gemm(GemmArgs g) {
 
   // element (row mt*32 + r32, k = kb*64 + half*32 + i*8 + e) of a tile sits
   // in chunk i of lane r32 + 32*half of row tile mt. The 8 MT staged chunks
-  // of a k-step (plane, row tile, chunk) are numbered q = (plane MT + mt) 4
-  // + chunk, and wave w stages q = w, w + NW, ...
+  // of a k-step (row tile, plane, chunk) are numbered q = (mt 2 + plane) 4 +
+  // chunk, their order in memory, and wave w stages q = w, w + NW, ...
   constexpr int NS = 8 * MT / NW;  // chunks staged per wave
   static_assert(NS >= 1 && NS * NW == 8 * MT, "staging split");
   const uint16_t* wp = g.W + (size_t)(active ? nb : 0) * 2048 + (size_t)lane * 8;
   const size_t wstep = (size_t)nblk * 2048;  // next k-step of the same column block
-  const uint16_t* sap[NS];
-  int s_pl[NS], s_mt[NS], s_ch[NS];
-#pragma unroll
-  for (int j = 0; j < NS; ++j) {
-    const int q = wave + NW * j;
-    s_ch[j] = q & 3;
-    s_mt[j] = (q >> 2) % MT;
-    s_pl[j] = (q >> 2) / MT;
-    sap[j] = (s_pl[j] ? g.A_lo : g.A) + (size_t)(s_mt[j] * 32 + r32) * g.lda + half * 32 + s_ch[j] * 8;
-  }
+  const uint16_t* ap = g.A + (size_t)wave * 512 + (size_t)lane * 8;
+  const size_t astep = (size_t)g.mtiles * 4096;
 
   f32x16 acc[MT];
 #pragma unroll
@@ -138,7 +137,7 @@ __global__ __launch_bounds__(NW * kWave) void k_gemm(GemmArgs g) {
   auto issue = [&](int t, int slot) {
     const int st = kstep(t);
 #pragma unroll
-    for (int j = 0; j < NS; ++j) ra[slot][j] = *(const u32x4*)(sap[j] + st * 64);
+    for (int j = 0; j < NS; ++j) ra[slot][j] = *(const u32x4*)(ap + (size_t)st * astep + j * NW * 512);
     const uint16_t* src = t < n ? wp + (size_t)st * wstep : wpad;
 #pragma unroll
     for (int i = 0; i < 4; ++i) w[slot][i] = __builtin_nontemporal_load((const u32x4*)(src + i * 512));
@@ -146,7 +145,7 @@ __global__ __launch_bounds__(NW * kWave) void k_gemm(GemmArgs g) {
   auto stage = [&](int t, int slot, int buf) {
     const u32x4 z = {0u, 0u, 0u, 0u};
 #pragma unroll
-    for (int j = 0; j < NS; ++j) sm.a[buf][s_pl[j]][s_mt[j]][s_ch[j]][lane] = t < n ? ra[slot][j] : z;
+    for (int j = 0; j < NS; ++j) (&sm.a[buf][0][0][0][0])[(wave + j * NW) * kWave + lane] = t < n ? ra[slot][j] : z;
   };
 
   if (n > 0) {
@@ -163,7 +162,7 @@ __global__ __launch_bounds__(NW * kWave) void k_gemm(GemmArgs g) {
       for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
-          const u32x4 ah = sm.a[u & 1][0][mt][i][lane], al = sm.a[u & 1][1][mt][i][lane];
+          const u32x4 ah = sm.a[u & 1][mt][0][i][lane], al = sm.a[u & 1][mt][1][i][lane];
           acc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(ah), as_bf16x8(w[u][i]), acc[mt], 0, 0, 0);
           acc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(al), as_bf16x8(w[u][i]), acc[mt], 0, 0, 0);
         }
@@ -239,7 +238,7 @@ int gemm_splits(int N, int K, int target_wgs, bool wide) {
 }
 
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
-  if (g.M < 1 || g.M > 128 || g.N % 32 || g.K % 64 || g.S < 1 || g.S > kGemmMaxSplits) return hipErrorInvalidValue;
+  if (g.M < 1 || g.M > 128 || g.M > 32 * g.mtiles || g.N % 32 || g.K % 64 || g.S < 1 || g.S > kGemmMaxSplits) return hipErrorInvalidValue;
   const int MT = (g.M + 31) / 32;
   if (g.cfg_rows < 0 || g.cfg_rows > 32 || (g.cfg_rows > 0 && (MT & 1))) return hipErrorInvalidValue;
   const int nw = g.wide ? kGWavesWide : kGWaves;
