@@ -44,6 +44,126 @@ struct AttnSmem {
   float l[4][32];
 };
 
+// One wave's 32 keys against 32 slots: its key and value tiles.
+template <int HD>
+struct KvTile {
+  uint4 kh[HD / 16], kl[HD / 16], vh[HD / 32][2], vl[HD / 32][2];
+};
+template <int HD>
+SJD_DEV void load_tile(KvTile<HD>& t, const uint16_t* kc, const uint16_t* kc_lo, const uint16_t* vt,
+                       const uint16_t* vt_lo, size_t ofs) {
+  const uint4 *kp = (const uint4*)(kc + ofs), *kpl = (const uint4*)(kc_lo + ofs);
+  const uint4 *vp = (const uint4*)(vt + ofs), *vpl = (const uint4*)(vt_lo + ofs);
+#pragma unroll
+  for (int i = 0; i < HD / 16; ++i) {
+    t.kh[i] = kp[i * 64];
+    t.kl[i] = kpl[i * 64];
+  }
+#pragma unroll
+  for (int d = 0; d < HD / 32; ++d)
+#pragma unroll
+    for (int jj = 0; jj < 2; ++jj) {
+      t.vh[d][jj] = vp[(d * 2 + jj) * 64];
+      t.vl[d][jj] = vpl[(d * 2 + jj) * 64];
+    }
+}
+
+// Scores of keys kb .. kb + 31 (q from LDS, Q^T operand order), their softmax
+// statistics (maximum in the log2 domain, sum) and the unnormalised output:
+// register r of o[d] holds dim d*32 + 8(r/4) + 4half + r%4 of this lane's slot.
+template <int HD>
+SJD_DEV void attn_wave(const AttnArgs& a, const KvTile<HD>& kv, const uint4 (&q)[2][HD / 16][kWave], int kb, int n,
+                       int nk, int gslot, bool slot_ok, f32x16 (&o)[HD / 32], float& m_w, float& l_w) {
+  const int lane = threadIdx.x & 63, half = lane >> 5;
+  f32x16 s;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) s[r] = 0.0f;
+#pragma unroll
+  for (int t = 0; t < HD / 16; ++t) {
+    const bf16x8 khb = to_bf16x8(kv.kh[t]), klb = to_bf16x8(kv.kl[t]);
+    const bf16x8 qh = to_bf16x8(q[0][t][lane]), ql = to_bf16x8(q[1][t][lane]);
+    s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(khb, qh, s, 0, 0, 0);
+    s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(khb, ql, s, 0, 0, 0);
+    s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(klb, qh, s, 0, 0, 0);
+  }
+  // mask (register r = 8jj + e holds key kb + 16jj + 8half + e): cached
+  // keys are visible to every slot, window keys by the ancestor mask
+  if (kb + 32 <= n) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] = slot_ok ? s[r] * a.scale : -INFINITY;
+  } else {
+    const uint64_t anc = slot_ok ? a.win->anc[gslot] : 0ull;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int key = kb + 16 * (r >> 3) + 8 * half + (r & 7);
+      bool vis = slot_ok && key < nk;
+      if (vis && key >= n) vis = (anc >> (key - n)) & 1ull;
+      s[r] = vis ? s[r] * a.scale : -INFINITY;
+    }
+  }
+  float mloc = s[0];
+#pragma unroll
+  for (int r = 1; r < 16; ++r) mloc = fmaxf(mloc, s[r]);
+  m_w = fmaxf(mloc, __shfl_xor(mloc, 32, kWave));
+  float lsum = 0.0f;
+  if (m_w != -INFINITY) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      s[r] = exp2f(s[r] - m_w);
+      lsum += s[r];
+    }
+  } else {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] = 0.0f;
+  }
+  l_w = lsum + __shfl_xor(lsum, 32, kWave);
+  // P^T operand (hi / lo bf16; P is finite, in [0, 1]) and O^T = V^T . P^T
+  uint4 pb[2], pbl[2];
+#pragma unroll
+  for (int jj = 0; jj < 2; ++jj) {
+    uint32_t w[4], wl[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      uint16_t h0, l0, h1, l1;
+      split_bf16_finite(s[8 * jj + 2 * e], h0, l0);
+      split_bf16_finite(s[8 * jj + 2 * e + 1], h1, l1);
+      w[e] = (uint32_t)h0 | ((uint32_t)h1 << 16);
+      wl[e] = (uint32_t)l0 | ((uint32_t)l1 << 16);
+    }
+    pb[jj] = make_uint4(w[0], w[1], w[2], w[3]);
+    pbl[jj] = make_uint4(wl[0], wl[1], wl[2], wl[3]);
+  }
+#pragma unroll
+  for (int d = 0; d < HD / 32; ++d)
+#pragma unroll
+    for (int jj = 0; jj < 2; ++jj) {
+      const bf16x8 vhb = to_bf16x8(kv.vh[d][jj]), vlb = to_bf16x8(kv.vl[d][jj]);
+      o[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vhb, to_bf16x8(pb[jj]), o[d], 0, 0, 0);
+      o[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vhb, to_bf16x8(pbl[jj]), o[d], 0, 0, 0);
+      o[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vlb, to_bf16x8(pb[jj]), o[d], 0, 0, 0);
+    }
+}
+
+// Merges a chunk's four waves (their outputs, maxima and sums in LDS) for one
+// slot's HD / 8 dims from d0: unnormalised output, maximum, sum.
+template <int HD>
+SJD_DEV void merge_waves(const float (*so)[32][HD + 1], const float (*smx)[32], const float (*sl_)[32], int sl, int d0,
+                         float (&v)[HD / 8], float& mx, float& ls) {
+  mx = smx[0][sl];
+#pragma unroll
+  for (int w = 1; w < 4; ++w) mx = fmaxf(mx, smx[w][sl]);
+  float f[4];
+  ls = 0.0f;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    f[w] = mx == -INFINITY ? 0.0f : exp2f(smx[w][sl] - mx);
+    ls += sl_[w][sl] * f[w];
+  }
+#pragma unroll
+  for (int i = 0; i < HD / 8; ++i)
+    v[i] = so[0][sl][d0 + i] * f[0] + so[1][sl][d0 + i] * f[1] + so[2][sl][d0 + i] * f[2] + so[3][sl][d0 + i] * f[3];
+}
+
 template <int HD>
 __global__ __launch_bounds__(256) void k_attn_partial(AttnArgs a) {
   constexpr int NQ = HD / 16;  // MFMAs per 32-key block for the scores
@@ -88,25 +208,8 @@ __global__ __launch_bounds__(256) void k_attn_partial(AttnArgs a) {
       qs[1][i] = (slot_ok && t < NQ) ? qpl[t] : make_uint4(0, 0, 0, 0);
     }
   }
-  uint4 kh[NQ], kl[NQ], vh[ND][2], vl[ND][2];
-  if (has) {
-    const uint4* kp = (const uint4*)(kc + tofs);
-    const uint4* kpl = (const uint4*)(kc_lo + tofs);
-#pragma unroll
-    for (int t = 0; t < NQ; ++t) {
-      kh[t] = kp[t * 64];
-      kl[t] = kpl[t * 64];
-    }
-    const uint4* vp = (const uint4*)(vt + tofs);
-    const uint4* vpl = (const uint4*)(vt_lo + tofs);
-#pragma unroll
-    for (int d = 0; d < ND; ++d)
-#pragma unroll
-      for (int jj = 0; jj < 2; ++jj) {
-        vh[d][jj] = vp[(d * 2 + jj) * 64];
-        vl[d][jj] = vpl[(d * 2 + jj) * 64];
-      }
-  }
+  KvTile<HD> kv;
+  if (has) load_tile<HD>(kv, kc, kc_lo, vt, vt_lo, tofs);
   // Q^T operand: lane (slot, half) holds dims half*HD/2 + 8t + e of its
   // slot; wave w staged chunks t = w, w + 4, ...
 #pragma unroll
@@ -125,75 +228,7 @@ __global__ __launch_bounds__(256) void k_attn_partial(AttnArgs a) {
 #pragma unroll
     for (int r = 0; r < 16; ++r) o[d][r] = 0.0f;
   float m_w = -INFINITY, l_w = 0.0f;
-  if (has) {
-    f32x16 s;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) s[r] = 0.0f;
-#pragma unroll
-    for (int t = 0; t < NQ; ++t) {
-      const bf16x8 khb = to_bf16x8(kh[t]), klb = to_bf16x8(kl[t]);
-      const bf16x8 qh = to_bf16x8(sm.q[0][t][lane]), ql = to_bf16x8(sm.q[1][t][lane]);
-      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(khb, qh, s, 0, 0, 0);
-      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(khb, ql, s, 0, 0, 0);
-      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(klb, qh, s, 0, 0, 0);
-    }
-    // mask (register r = 8jj + e holds key kb + 16jj + 8half + e): cached
-    // keys are visible to every slot, window keys by the ancestor mask
-    if (kb + 32 <= n) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) s[r] = slot_ok ? s[r] * a.scale : -INFINITY;
-    } else {
-      const uint64_t anc = slot_ok ? a.win->anc[gslot] : 0ull;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int key = kb + 16 * (r >> 3) + 8 * half + (r & 7);
-        bool vis = slot_ok && key < nk;
-        if (vis && key >= n) vis = (anc >> (key - n)) & 1ull;
-        s[r] = vis ? s[r] * a.scale : -INFINITY;
-      }
-    }
-    float mloc = s[0];
-#pragma unroll
-    for (int r = 1; r < 16; ++r) mloc = fmaxf(mloc, s[r]);
-    m_w = fmaxf(mloc, __shfl_xor(mloc, 32, kWave));
-    float lsum = 0.0f;
-    if (m_w != -INFINITY) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        s[r] = exp2f(s[r] - m_w);
-        lsum += s[r];
-      }
-    } else {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) s[r] = 0.0f;
-    }
-    l_w = lsum + __shfl_xor(lsum, 32, kWave);
-    // P^T operand (hi / lo bf16; P is finite, in [0, 1]) and O^T = V^T . P^T
-    uint4 pb[2], pbl[2];
-#pragma unroll
-    for (int jj = 0; jj < 2; ++jj) {
-      uint32_t w[4], wl[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        uint16_t h0, l0, h1, l1;
-        split_bf16_finite(s[8 * jj + 2 * e], h0, l0);
-        split_bf16_finite(s[8 * jj + 2 * e + 1], h1, l1);
-        w[e] = (uint32_t)h0 | ((uint32_t)h1 << 16);
-        wl[e] = (uint32_t)l0 | ((uint32_t)l1 << 16);
-      }
-      pb[jj] = make_uint4(w[0], w[1], w[2], w[3]);
-      pbl[jj] = make_uint4(wl[0], wl[1], wl[2], wl[3]);
-    }
-#pragma unroll
-    for (int d = 0; d < ND; ++d)
-#pragma unroll
-      for (int jj = 0; jj < 2; ++jj) {
-        const bf16x8 vhb = to_bf16x8(vh[d][jj]), vlb = to_bf16x8(vl[d][jj]);
-        o[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vhb, to_bf16x8(pb[jj]), o[d], 0, 0, 0);
-        o[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vhb, to_bf16x8(pbl[jj]), o[d], 0, 0, 0);
-        o[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vlb, to_bf16x8(pb[jj]), o[d], 0, 0, 0);
-      }
-  }
+  if (has) attn_wave<HD>(a, kv, sm.q, kb, n, nk, gslot, slot_ok, o, m_w, l_w);
 
   // ---- merge the four waves (the merge buffer overlays q: wait for every
   // wave's scores first). Output register r of block d holds dim
@@ -211,29 +246,11 @@ __global__ __launch_bounds__(256) void k_attn_partial(AttnArgs a) {
   // thread -> (slot, HD/8 consecutive dims)
   constexpr int DPT = HD / 8;
   const int sl = threadIdx.x >> 3, d0 = (threadIdx.x & 7) * DPT;
-  float mx = sm.m[0][sl];
-#pragma unroll
-  for (int w = 1; w < 4; ++w) mx = fmaxf(mx, sm.m[w][sl]);
-  float f[4], ls = 0.0f;
-#pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    f[w] = mx == -INFINITY ? 0.0f : exp2f(sm.m[w][sl] - mx);
-    ls += sm.l[w][sl] * f[w];
-  }
+  float v[DPT], mx, ls;
+  merge_waves<HD>(sm.o, sm.m, sm.l, sl, d0, v, mx, ls);
   float* wo = a.ws_o + (((size_t)h * a.nsplit_max + sp) * kWinRows + zs + sl) * HD + d0;
 #pragma unroll
-  for (int i = 0; i < DPT; i += 4) {
-    float4 v;
-    v.x = sm.o[0][sl][d0 + i] * f[0] + sm.o[1][sl][d0 + i] * f[1] + sm.o[2][sl][d0 + i] * f[2] +
-          sm.o[3][sl][d0 + i] * f[3];
-    v.y = sm.o[0][sl][d0 + i + 1] * f[0] + sm.o[1][sl][d0 + i + 1] * f[1] + sm.o[2][sl][d0 + i + 1] * f[2] +
-          sm.o[3][sl][d0 + i + 1] * f[3];
-    v.z = sm.o[0][sl][d0 + i + 2] * f[0] + sm.o[1][sl][d0 + i + 2] * f[1] + sm.o[2][sl][d0 + i + 2] * f[2] +
-          sm.o[3][sl][d0 + i + 2] * f[3];
-    v.w = sm.o[0][sl][d0 + i + 3] * f[0] + sm.o[1][sl][d0 + i + 3] * f[1] + sm.o[2][sl][d0 + i + 3] * f[2] +
-          sm.o[3][sl][d0 + i + 3] * f[3];
-    *(float4*)(wo + i) = v;
-  }
+  for (int i = 0; i < DPT; i += 4) *(float4*)(wo + i) = make_float4(v[i], v[i + 1], v[i + 2], v[i + 3]);
   if ((threadIdx.x & 7) == 0) {
     float* wml = a.ws_ml + ((size_t)h * a.nsplit_max + sp) * kWinRows * 2 + (size_t)(zs + sl) * 2;
     wml[0] = mx;
@@ -524,6 +541,107 @@ __global__ __launch_bounds__(64) void k_attn_combine(AttnArgs a) {
   store_act<8>(out, acc);
 }
 
+// Attention of narrow models over short caches in one kernel: one workgroup per
+// query head and 32 slots takes two chunks at a time (8 waves, the next two's
+// tiles in flight), keeps the chunks' partials on chip and combines them, with the arithmetic and orders
+// of k_attn_partial and k_attn_combine (the same bits). What it saves is the
+// second launch and the partials' trip through memory; its H workgroups read
+// the cache with few compute units, so it pays only while that is short
+// (kWholeChunks, at 16 heads x 64 dims).
+constexpr int kWholeIters = (kWholeChunks + 1) / 2;
+template <int HD>
+struct AttnWholeSmem {
+  float o[8][32][HD + 1];              // the waves' outputs of two chunks
+  float part[2 * kWholeIters][32][HD];  // the chunks' merged outputs
+  uint4 q[2][HD / 16][kWave];
+  float m[8][32], l[8][32];
+  float2 ml[2 * kWholeIters][32];
+};
+template <int HD>
+__global__ __launch_bounds__(512) void k_attn_whole(AttnArgs a) {
+  constexpr int NQ = HD / 16, ND = HD / 32, DPT = HD / 8;
+  static_assert(2 * NQ <= 8 && DPT == 8, "one q chunk per wave; 8 dims per combining thread");
+  __shared__ AttnWholeSmem<HD> sm;
+  const int h = blockIdx.x, z = blockIdx.y;
+  const bool two = a.st.mode != kStreamsOne;
+  const int n = stream_rows(a.st, a.n_dev ? *a.n_dev : a.n_host, z);
+  const int Ms = two ? a.st.L : a.M, nk = n + Ms;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, slot = lane & 31, half = lane >> 5;
+  const int grp = wave >> 2;  // chunk of this wave within an iteration
+  const int zs = z * 32, gslot = zs + slot;
+  const bool slot_ok = two ? slot < Ms : gslot < Ms;
+  const size_t hb = (size_t)(h / (a.H / a.Hkv)) * a.cap * HD + (two ? (size_t)z * a.sstride : 0);
+  if (wave < 2 * NQ) {
+    const int p = wave / NQ, t = wave % NQ;
+    const size_t qo = (size_t)(slot_ok ? gslot : 0) * a.H * HD + (size_t)h * HD + half * (HD / 2);
+    const uint4* qp = (const uint4*)((p ? a.q_lo : a.q) + qo);
+    sm.q[p][t][lane] = slot_ok ? qp[t] : make_uint4(0, 0, 0, 0);
+  }
+  // merge thread: slot sl, dims d0 .. d0 + 7 of chunk `grp` of each iteration
+  const int t256 = threadIdx.x & 255, sl = t256 >> 3, d0 = (t256 & 7) * DPT;
+  auto block_of = [&](int it) { return (it * 2 + grp) * kAttnChunk + (wave & 3) * 32; };
+  // (a block past the capacity re-reads block 0; what lies past the keys is not
+  // used). The first chunks' tiles do not wait for the key count.
+  auto load = [&](KvTile<HD>& t, int it) {
+    const int kb = block_of(it);
+    load_tile<HD>(t, a.kc, a.kc_lo, a.vt, a.vt_lo, hb + (size_t)(kb < a.cap ? kb : 0) * HD + (size_t)lane * 8);
+  };
+  KvTile<HD> tile[2];
+  load(tile[0], 0);
+  const int nch = (nk + kAttnChunk - 1) / kAttnChunk;
+#pragma unroll
+  for (int it = 0; it < kWholeIters; ++it) {
+    if (it * 2 >= nch) break;  // uniform over the workgroup
+    const int kb = block_of(it);
+    const bool has = kb < nk;
+    if (it + 1 < kWholeIters && (it + 1) * 2 < nch) load(tile[(it + 1) & 1], it + 1);
+    f32x16 o[ND];
+#pragma unroll
+    for (int d = 0; d < ND; ++d)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[d][r] = 0.0f;
+    float m_w = -INFINITY, l_w = 0.0f;
+    __syncthreads();  // q is in LDS; the previous iteration's outputs are merged
+    if (has) attn_wave<HD>(a, tile[it & 1], sm.q, kb, n, nk, gslot, slot_ok, o, m_w, l_w);
+#pragma unroll
+    for (int d = 0; d < ND; ++d)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) sm.o[wave][slot][d * 32 + 8 * (r >> 2) + 4 * half + (r & 3)] = o[d][r];
+    if (half == 0) {
+      sm.m[wave][slot] = m_w;
+      sm.l[wave][slot] = l_w;
+    }
+    __syncthreads();
+    float v[DPT], mx, ls;
+    merge_waves<HD>(&sm.o[4 * grp], &sm.m[4 * grp], &sm.l[4 * grp], sl, d0, v, mx, ls);
+    float* p = &sm.part[it * 2 + grp][sl][d0];
+    *(float4*)p = make_float4(v[0], v[1], v[2], v[3]);
+    *(float4*)(p + 4) = make_float4(v[4], v[5], v[6], v[7]);
+    if (d0 == 0) sm.ml[it * 2 + grp][sl] = make_float2(mx, ls);
+  }
+  __syncthreads();
+  if (threadIdx.x >= 256 || zs + sl >= a.M) return;
+  uint16_t* out = a.out + act_off(zs + sl, h * HD + d0, a.mtiles);
+  if (two && sl >= a.st.L) {  // padding row of a multi-stream window: finite zeros
+    *(uint4*)out = make_uint4(0, 0, 0, 0);
+    *(uint4*)(out + kActLo) = make_uint4(0, 0, 0, 0);
+    return;
+  }
+  float gm = -INFINITY, lt = 0.0f;
+  for (int i = 0; i < nch; ++i) gm = fmaxf(gm, sm.ml[i][sl].x);
+  float acc[DPT] = {};
+  for (int i = 0; i < nch; ++i) {
+    const float2 ml = sm.ml[i][sl];
+    const float f = ml.x == -INFINITY ? 0.0f : exp2f(ml.x - gm);
+    lt += ml.y * f;
+#pragma unroll
+    for (int e = 0; e < DPT; ++e) acc[e] += sm.part[i][sl][d0 + e] * f;
+  }
+#pragma unroll
+  for (int e = 0; e < DPT; ++e) acc[e] /= lt;
+  store_act<8>(out, acc);
+}
+
 hipError_t launch_attention(const AttnArgs& a, int hd, hipStream_t s) {
   if (a.M > 32 * a.mtiles) return hipErrorInvalidValue;
   if (a.M < 1 || a.M > (a.st.mode == kStreamsOne ? 64 : 32 * kMaxStreams)) return hipErrorInvalidValue;
@@ -538,6 +656,8 @@ hipError_t launch_attention(const AttnArgs& a, int hd, hipStream_t s) {
     if (G / a.qparts > 1) hipLaunchKernelGGL(k_attn_partial_px<true>, gp, dim3(256), 0, s, a);
     else hipLaunchKernelGGL(k_attn_partial_px<false>, gp, dim3(256), 0, s, a);
     hipLaunchKernelGGL(k_attn_combine<128>, g2, dim3(64), 0, s, a);
+  } else if (hd == 64 && a.whole && a.nsplit_max <= kWholeChunks) {
+    hipLaunchKernelGGL(k_attn_whole<64>, dim3(a.H, zh), dim3(512), 0, s, a);
   } else if (hd == 64) {
     hipLaunchKernelGGL(k_attn_partial<64>, g1, dim3(256), 0, s, a);
     hipLaunchKernelGGL(k_attn_combine<64>, g2, dim3(64), 0, s, a);

@@ -71,6 +71,13 @@ SJD_DEV void split_bf16(float v, uint16_t& hi, uint16_t& lo) {
   lo = f32_to_bf16(v - bf16_to_f32(hi));
 }
 
+// Rotary pair (a, b) by the angle (cos, sin) = cs, with the contractions spelled
+// out so that every kernel that rotates rounds alike
+SJD_DEV void rotate_pair(float a, float b, const float2& cs, float& o0, float& o1) {
+  o0 = __builtin_fmaf(a, cs.x, -(b * cs.y));
+  o1 = __builtin_fmaf(b, cs.x, a * cs.y);
+}
+
 // C (4 or 8) consecutive columns of one activation row as hi / lo bf16: the hi
 // plane of their tile at y, the lo plane kActLo elements on (forward.h's
 // activation tiles)
@@ -147,6 +154,18 @@ SJD_DEV int wave_incl_scan(int v) {
   return v;
 }
 
+
+// Sum of 64 floats at p (16-byte aligned) in the order of wave_sum's butterfly
+SJD_DEV float butterfly64(const float* p) {
+  float v[64];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) *(float4*)&v[4 * i] = ((const float4*)p)[i];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+    for (int l = 0; l < o; ++l) v[l] += v[l + o];
+  return v[0];
+}
 
 // --------------------------------------------- DPP reductions (all lanes on)
 // Cross-lane steps through DPP instead of the LDS permute network: within

@@ -1,4 +1,4 @@
-// Small kernels of the window forward: embedding gather, RMSNorm, rotary
+// Small kernels of the window forward: window rows and embedding, RMSNorm, rotary
 // embedding with the key/value cache write, and weight conversion.
 #include <type_traits>
 
@@ -6,33 +6,6 @@
 #include "forward.h"
 
 namespace sjd {
-
-// x[m][:] = E[tok[m]][:] (fp32 residual stream); d is a multiple of 64, so
-// every 8-element chunk is whole. Token ids come from callers (prompts,
-// drafts); an id outside [0, vocab) is read as token `fallback`, so no read
-// leaves the embedding table.
-__global__ __launch_bounds__(256) void k_embed(const uint16_t* E, const Window* win, int d, int vocab, int fallback,
-                                               float* x) {
-  const int m = blockIdx.x;
-  int t = win->tok[m];
-  t = (t >= 0 && t < vocab) ? t : fallback;
-  const uint4* row = (const uint4*)(E + (size_t)t * d);
-  float4* xr = (float4*)(x + (size_t)m * d);
-  for (int c = threadIdx.x; c < d / 8; c += blockDim.x) {
-    const uint4 u = row[c];
-    xr[2 * c] = make_float4(__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xFFFF0000u),
-                            __uint_as_float(u.y << 16), __uint_as_float(u.y & 0xFFFF0000u));
-    xr[2 * c + 1] = make_float4(__uint_as_float(u.z << 16), __uint_as_float(u.z & 0xFFFF0000u),
-                                __uint_as_float(u.w << 16), __uint_as_float(u.w & 0xFFFF0000u));
-  }
-}
-
-hipError_t launch_embed(const uint16_t* E, const Window* win, int M, int d, int vocab, int fallback, float* x,
-                        hipStream_t s) {
-  if (fallback < 0 || fallback >= vocab) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_embed, dim3(M), dim3(256), 0, s, E, win, d, vocab, fallback, x);
-  return hipGetLastError();
-}
 
 // acc[0..C) += sum_s of C consecutive floats of S partial planes, in plane
 // order. The planes were written moments ago by workgroups on every XCD, so
@@ -68,11 +41,12 @@ constexpr int kNarrowWaves = 512;  // C = 4 where C = 8 would give fewer waves
 // x += sum_s part[s] (split-K partial planes of the projection that feeds
 // the residual, fixed order), y = x * g as tiled activations, ss[m][c] = sum
 // of x^2 over the 256 elements of chunk c, each four of them in order and then
-// by a butterfly over the 64 fours. grid (chunks, rows / 8), 32 / C waves.
+// by a butterfly over the 64 fours (narrow models: the fours themselves, [m][64
+// chunks]). grid (chunks, rows / 8), 32 / C waves.
 template <int G, int C>
 __global__ __launch_bounds__(2048 / C) void k_resid_norm(float* x, const float* part, int S, size_t plane,
                                                          const uint16_t* g, int M, int d, uint16_t* y, int mtiles,
-                                                         float* ss) {
+                                                         float* ss, float* fours) {
   __shared__ float four[8][kWave];
   const int c = blockIdx.x, wave = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
   const int m = blockIdx.y * 8 + (lane >> 3), i0 = c * 256 + wave * 8 * C + (lane & 7) * C;
@@ -99,6 +73,12 @@ __global__ __launch_bounds__(2048 / C) void k_resid_norm(float* x, const float* 
     for (int e = 0; e < C; ++e) v[e] *= bf16_to_f32(gg[e]);
     store_act<C>(y + act_off(m, i0, mtiles), v);
   }
+  if (fours) {  // uniform over the grid
+    if (m < M && i0 < d)
+#pragma unroll
+      for (int i = 0; i < C / 4; ++i) fours[(size_t)m * gridDim.x * 64 + (i0 >> 2) + i] = sq[i];
+    return;
+  }
 #pragma unroll
   for (int i = 0; i < C / 4; ++i) four[lane >> 3][(wave * 8 + (lane & 7)) * (C / 4) + i] = sq[i];
   __syncthreads();
@@ -112,7 +92,7 @@ __global__ __launch_bounds__(2048 / C) void k_resid_norm(float* x, const float* 
 }
 
 hipError_t launch_resid_norm(float* x, const float* part, int S, size_t plane, const uint16_t* g, int M, int d,
-                             uint16_t* y, int mtiles, float* ss, hipStream_t s) {
+                             uint16_t* y, int mtiles, float* ss, float* fours, hipStream_t s) {
   if (S < 0 || S > kGemmMaxSplits || M > 32 * mtiles) return hipErrorInvalidValue;
   const dim3 grid(norm_chunks(d), (M + 7) / 8);
   auto go = [&](auto c) {
@@ -121,10 +101,110 @@ hipError_t launch_resid_norm(float* x, const float* part, int S, size_t plane, c
                    : S <= 8  ? k_resid_norm<8, C>
                    : S <= 16 ? k_resid_norm<16, C>
                              : k_resid_norm<kGemmMaxSplits, C>;
-    hipLaunchKernelGGL(k, grid, dim3(2048 / C), 0, s, x, part, S, plane, g, M, d, y, mtiles, ss);
+    hipLaunchKernelGGL(k, grid, dim3(2048 / C), 0, s, x, part, S, plane, g, M, d, y, mtiles, ss, fours);
   };
   if ((d / 64) * ((M + 7) / 8) < kNarrowWaves / 2) go(std::integral_constant<int, 4>{});
   else go(std::integral_constant<int, 8>{});
+  return hipGetLastError();
+}
+
+// Window layout (Sec. 3.3: L verified positions per forward; Sec. 4.1: K
+// candidates at each of the first D positions after a rejection): slot 0 holds
+// the pending token (last committed, not yet cached) at position n; slot i, 1 <=
+// i < n_s, holds spine draft i-1 at n + i; slot n_s + d(K-1) + k-2 holds sibling
+// k of depth d at n + 1 + d and sees slots 0..d and itself. A missing sibling
+// slot is fed token vis_lo.
+SJD_DEV void window_row(const WindowIn& in, int a, int& tok, int& pos, uint64_t& anc) {
+  if (!in.st) {  // prefill: a causal chain
+    tok = in.prompt[in.start + a];
+    pos = in.start + a;
+    anc = a == 63 ? ~0ull : ((1ull << (a + 1)) - 1ull);
+    return;
+  }
+  const Streams& sm = in.sm;
+  const bool multi = sm.mode != kStreamsOne;
+  const int z = multi ? a >> 5 : 0;      // stream of this row
+  const int loc = multi ? (a & 31) : a;  // window row within its stream
+  if (loc >= in.L) {  // padding row of a multi-stream window: never read, never cached
+    tok = in.vis_lo;
+    pos = in.st->n;
+    anc = 0ull;
+    return;
+  }
+  // batched: stream z is image z; guided: streams 2b, 2b + 1 are image b
+  const DevState* d = multi ? in.st + stream_image(sm, z) : in.st;
+  const bool unc = multi && stream_uncond(sm, z);
+  const int n = d->n, n_s = d->n_s;
+  // both words that the row may need, loaded before n_s is known
+  const int chain = loc == 0 ? (unc ? d->pending_u : d->pending) : d->spine[loc - 1];
+  if (loc < n_s) {
+    tok = chain;
+    pos = n + loc;
+    anc = loc == 63 ? ~0ull : ((1ull << (loc + 1)) - 1ull);
+  } else {
+    const int t = loc - n_s, dd = t / (in.K - 1), k = t % (in.K - 1);
+    const int y = d->sib[dd * (in.K - 1) + k];
+    tok = y >= 0 ? y : in.vis_lo;
+    pos = n + 1 + dd;
+    anc = ((1ull << (dd + 1)) - 1ull) | (1ull << loc);
+  }
+  if (unc) pos += d->delta_u;
+}
+
+// One launch for what were three (window build, embedding gather, first norm),
+// each of which took 4-5 us of the step for a few hundred KB: the rows' tokens
+// are a few words of cached state, so every workgroup derives its own. grid
+// (256-column chunks, rows / 8), four waves of 8 rows x 64 columns. Token ids
+// come from callers (prompts, drafts): none is used as an index unchecked.
+__global__ __launch_bounds__(256) void k_window_in(WindowIn a) {
+  __shared__ float four[8][kWave];
+  const int c = blockIdx.x, wave = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
+  const int m = blockIdx.y * 8 + (lane >> 3), i0 = c * 256 + wave * 64 + (lane & 7) * 8;
+  float s0 = 0.0f, s1 = 0.0f;
+  if (m < a.M) {
+    int tok, pos;
+    uint64_t anc;
+    window_row(a, m, tok, pos, anc);
+    if (c == 0 && wave == 0 && (lane & 7) == 0) {
+      a.win->tok[m] = tok;
+      a.win->pos[m] = pos;
+      a.win->anc[m] = anc;
+    }
+    tok = (tok >= 0 && tok < a.vocab) ? tok : a.vis_lo;
+    if (i0 < a.d) {  // d is a multiple of 64: a lane's 8 columns are all in range
+      const uint4 u = *(const uint4*)(a.E + (size_t)tok * a.d + i0), gu = *(const uint4*)(a.g + i0);
+      const uint32_t uw[4] = {u.x, u.y, u.z, u.w}, gw[4] = {gu.x, gu.y, gu.z, gu.w};
+      float v[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = __uint_as_float(e & 1 ? uw[e >> 1] & 0xFFFF0000u : uw[e >> 1] << 16);
+      float* xr = a.x + (size_t)m * a.d + i0;
+      *(float4*)xr = make_float4(v[0], v[1], v[2], v[3]);
+      *(float4*)(xr + 4) = make_float4(v[4], v[5], v[6], v[7]);
+      s0 = v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
+      s1 = v[4] * v[4] + v[5] * v[5] + v[6] * v[6] + v[7] * v[7];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] *= __uint_as_float(e & 1 ? gw[e >> 1] & 0xFFFF0000u : gw[e >> 1] << 16);
+      store_act<8>(a.y + act_off(m, i0, a.mtiles), v);
+      if (a.fours) *(float2*)(a.fours + (size_t)m * gridDim.x * 64 + (i0 >> 2)) = make_float2(s0, s1);
+    }
+  }
+  if (a.fours) return;  // uniform over the grid
+  *(float2*)&four[lane >> 3][wave * 16 + (lane & 7) * 2] = make_float2(s0, s1);
+  __syncthreads();
+#pragma unroll
+  for (int r = 2 * wave; r < 2 * wave + 2; ++r) {
+    const float ssq = wave_sum(four[r][lane]);
+    const int row = blockIdx.y * 8 + r;
+    if (lane == 0 && row < a.M) a.ss[(size_t)row * gridDim.x + c] = ssq;
+  }
+}
+
+hipError_t launch_window_in(const WindowIn& a, hipStream_t s) {
+  const bool multi = a.sm.mode != kStreamsOne;
+  if (a.M < 1 || a.M > kWinRows || a.M > 32 * a.mtiles || a.vis_lo < 0 || a.vis_lo >= a.vocab || (!a.st && !a.prompt) ||
+      (multi && (a.sm.nz < 1 || a.sm.nz > kMaxStreams || a.L > 32)) || (!multi && a.M > 64))
+    return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_window_in, dim3(norm_chunks(a.d), (a.M + 7) / 8), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
@@ -181,8 +261,8 @@ __global__ void k_rope_kv(const float* qkv, int S, size_t plane, const Window* w
     }
   if (hh < H + Hkv) {
     const float2 cs = rope[(size_t)win->pos[m] * half + i];
-    const float o0 = a * cs.x - b * cs.y;
-    const float o1 = a * cs.y + b * cs.x;
+    float o0, o1;
+    rotate_pair(a, b, cs, o0, o1);
     if (hh < H) {
       const size_t off = (size_t)m * H * hd + (size_t)hh * hd;
       split_bf16(o0, o.q[off + i], o.q_lo[off + i]);
@@ -256,7 +336,7 @@ hipError_t launch_swiglu(const float* P, int S, size_t plane, int M, int F, uint
 
 // one thread per 8-element chunk of the tiled layout
 __global__ void k_tile_weights(const void* src, int is_f32, size_t row0, int N, int K, uint16_t* dst,
-                               int nblk_total, int nb0) {
+                               int nblk_total, int nb0, int pair) {
   const size_t T = (size_t)K / 64;
   const size_t nchunks = (size_t)N / 32 * T * 256;
   for (size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x; q < nchunks; q += (size_t)gridDim.x * blockDim.x) {
@@ -275,19 +355,31 @@ __global__ void k_tile_weights(const void* src, int is_f32, size_t row0, int N, 
 #pragma unroll
       for (int e = 0; e < 8; ++e) v[e] = p[e];
     }
-    uint16_t* d = dst + ((kb * nblk_total + nb0 + nb) * 256 + within) * 8;
+    const int r = (int)nb * 32 + l % 32;
+    size_t ob = nb;
+    int ol = l;
+    if (pair > 0) {
+      const int j = r % pair;
+      ob = (size_t)(r / pair) * (pair / 32) + (j % (pair / 2)) / 16;
+      ol = (l & 32) + j % 16 + (j >= pair / 2 ? 16 : 0);
+    } else if (pair < 0) {
+      ob = (size_t)(r / 16);
+      ol = (l & 32) + r % 16 + (pair == -2 ? 16 : 0);
+    }
+    uint16_t* d = dst + ((kb * nblk_total + nb0 + ob) * 256 + (size_t)i * 64 + ol) * 8;
 #pragma unroll
     for (int e = 0; e < 8; ++e) d[e] = v[e];
   }
 }
 
 hipError_t launch_tile_weights(const void* src, int is_f32, size_t row0, int N, int K, uint16_t* dst,
-                               int nblk_total, int nb0, hipStream_t s) {
+                               int nblk_total, int nb0, int pair, hipStream_t s) {
+  if (pair > 0 && (pair % 32 || N % pair)) return hipErrorInvalidValue;
   size_t n = (size_t)N / 32 * (K / 64) * 256;
   size_t blocks = (n + 255) / 256;
   if (blocks > 65535 * 8) blocks = 65535 * 8;
   hipLaunchKernelGGL(k_tile_weights, dim3((unsigned)blocks), dim3(256), 0, s, src, is_f32, row0, N, K, dst,
-                     nblk_total, nb0);
+                     nblk_total, nb0, pair);
   return hipGetLastError();
 }
 

@@ -70,6 +70,11 @@ struct Ctx {
   float* rpart = nullptr;  // split-K partial planes of the O / down projections
   float* gup = nullptr;    // split-K partial planes of the gate / up projection [S_gu][Mpad][2F]
   float* ss = nullptr;     // RMSNorm chunk sums of squares [Mpad][norm_chunks(d)]
+  // Narrow models run each projection with its consumer as one kernel
+  // (fused.hip; the same bits as the split kernels under the same plan); they
+  // need no partial planes and keep the norm's sums by fours of columns
+  bool fused = false;
+  float* fours = nullptr;  // [Mpad][norm_chunks(d) * 64]
   sjd::DevState* st = nullptr;
   sjd::Window* win = nullptr;
   int32_t* rec = nullptr;
@@ -155,16 +160,37 @@ int check_config(const sjd_config* c) {
     if ((e) != hipSuccess) return SJD_EHIP;      \
   } while (0)
 
+// Models whose projections run with their consumers as one kernel each. Every
+// workgroup of such a projection reads the whole activation, 128 bytes per k and
+// row tile, so the line lies where that stops being cheap beside the launch it
+// saves: see fused.hip.
+// Their residual projections are one kernel up to K = 1024 (7.0 us at d = 1024,
+// where GEMM and norm take 11.2); at K = 2816 the 32 workgroups' 540 KB each
+// arrive too slowly (13.8 us against 11.8).
+constexpr int kFusedResidK = 1536;
+bool fused_shape(const sjd_config& c) {
+  return sjd::norm_chunks(c.d_model) <= sjd::kFusedMaxChunks && c.n_heads * c.head_dim <= 4096 && c.ffn_dim <= 4096;
+}
+
+// The LM head (unsplit) takes 8 column blocks per workgroup from this many columns
+// (192 workgroups) on, else 4 (twice the workgroups)
+constexpr int kWideHeadV = 192 * 256;
+
 enum { kProjQkv = 0, kProjO = 1, kProjGu = 2, kProjDown = 3 };
 
 // Window forward of M rows: two streams (sm.mode != kStreamsOne, see
-// Streams), or one stream on the caches of stream `cache` (a prefill).
-int forward(Ctx& x, int M, const int32_t* n_dev, int n_host, float* logits, const sjd::Streams& sm, int cache,
-            hipStream_t s) {
+// Streams), or one stream on the caches of stream `cache`. The rows come from
+// the decoder state, or (prefill) from prompt[n_host ..).
+int forward(Ctx& x, int M, const int32_t* prompt, const int32_t* n_dev, int n_host, float* logits,
+            const sjd::Streams& sm, int cache, hipStream_t s) {
   const sjd_config& c = x.c;
   const int d = c.d_model, H = c.n_heads, Hkv = c.n_kv_heads, hd = c.head_dim, F = c.ffn_dim;
   const int Nq = H * hd, Nkv = Hkv * hd, Nqkv = Nq + 2 * Nkv;
-  HIPTRY(sjd::launch_embed(x.embed, x.win, M, d, c.vocab_size, c.vis_lo, x.x, s));
+  sjd::WindowIn in{};
+  in.st = prompt ? nullptr : x.st; in.prompt = prompt; in.start = n_host; in.M = M; in.L = c.L; in.K = c.K;
+  in.vis_lo = c.vis_lo; in.sm = sm; in.win = x.win; in.E = x.embed; in.d = d; in.vocab = c.vocab_size; in.x = x.x;
+  in.g = x.lw[0][0]; in.y = x.xn; in.mtiles = x.mtiles; in.ss = x.ss; in.fours = x.fours;
+  HIPTRY(sjd::launch_window_in(in, s));
   const size_t qplane = (size_t)x.Mpad * Nqkv, rplane = (size_t)x.Mpad * d, guplane = (size_t)x.Mpad * 2 * F;
   int pend = 0;  // partial planes of the last residual projection not yet added into x
   const Ctx::Plan* P = M > 64 ? x.plan_wide : x.plan[M > 32 ? 1 : 0];
@@ -177,26 +203,56 @@ int forward(Ctx& x, int M, const int32_t* n_dev, int n_host, float* logits, cons
     const auto& w = x.lw[l];
     const size_t lofs = (size_t)l * Hkv * x.cap_pad * hd + (size_t)cache * x.kv_elems;
     sjd::KvPlanes kv{x.q, x.q_lo, x.kc + lofs, x.kc_lo + lofs, x.vt + lofs, x.vt_lo + lofs, x.kv_elems};
-    HIPTRY(sjd::launch_resid_norm(x.x, x.rpart, pend, rplane, w[0], M, d, x.xn, x.mtiles, x.ss, s));
-    sjd::GemmArgs g = normed;
-    g.A = x.xn; g.mtiles = x.mtiles; g.M = M; g.W = w[1]; g.N = Nqkv; g.K = d; g.S = P[kProjQkv].S;
-    g.wide = P[kProjQkv].wide; g.out = x.qkv; g.plane = qplane; g.ldo = Nqkv;
-    HIPTRY(sjd::launch_gemm(g, s));
-    HIPTRY(sjd::launch_rope_kv(x.qkv, P[kProjQkv].S, qplane, x.win, n_dev, n_host, M, H, Hkv, hd, x.rope, kv, x.cap_pad,
-                               sm, s));
     sjd::AttnArgs a{};
     a.q = x.q; a.q_lo = x.q_lo; a.kc = kv.kc; a.kc_lo = kv.kc_lo; a.vt = kv.vt; a.vt_lo = kv.vt_lo; a.win = x.win;
     a.sstride = kv.sstride; a.st = sm;
     a.n_dev = n_dev; a.n_host = n_host; a.M = M; a.H = H; a.Hkv = Hkv; a.cap = x.cap_pad;
     a.scale = (float)(1.4426950408889634 / std::sqrt((double)hd));
     a.ws_o = x.attn_o; a.ws_ml = x.attn_ml; a.nsplit_max = x.nsplit_max; a.out = x.att;
-    a.mtiles = x.mtiles; a.qparts = x.qparts;
+    a.mtiles = x.mtiles; a.qparts = x.qparts; a.whole = x.fused ? 1 : 0;
+    if (x.fused) {
+      sjd::FusedArgs f{};
+      f.mtiles = x.mtiles; f.M = M; f.inv_d = 1.0f / (float)d; f.eps = c.rms_eps;
+      f.nch = f.nch_out = sjd::norm_chunks(d); f.fours = f.fours_out = x.fours; f.x = x.x;
+      f.win = x.win; f.n_dev = n_dev; f.n_host = n_host; f.H = H; f.Hkv = Hkv; f.hd = hd; f.cap = x.cap_pad;
+      f.rope = x.rope; f.kv = kv; f.st = sm;
+      f.A = x.xn; f.W = w[1]; f.N = Nqkv; f.K = d; f.S = P[kProjQkv].S;
+      HIPTRY(sjd::launch_gemm_fused(sjd::kFusedRope, f, s));
+      HIPTRY(sjd::launch_attention(a, hd, s));
+      // x += A . W, then x normed by g: one kernel, or (long K) GEMM and norm
+      auto resid = [&](const uint16_t* A, const uint16_t* W, int K, int S, int wide, const uint16_t* gain) -> int {
+        if (K <= kFusedResidK) {
+          f.A = A; f.W = W; f.N = d; f.K = K; f.S = S; f.g = gain; f.y = x.xn;
+          HIPTRY(sjd::launch_gemm_fused(sjd::kFusedResid, f, s));
+          return SJD_OK;
+        }
+        sjd::GemmArgs g{};
+        g.A = A; g.mtiles = x.mtiles; g.M = M; g.W = W; g.N = d; g.K = K; g.S = S; g.wide = wide;
+        g.out = x.rpart; g.plane = rplane; g.ldo = d;
+        HIPTRY(sjd::launch_gemm(g, s));
+        HIPTRY(sjd::launch_resid_norm(x.x, x.rpart, S, rplane, gain, M, d, x.xn, x.mtiles, nullptr, x.fours, s));
+        return SJD_OK;
+      };
+      TRY(resid(x.att, w[4], Nq, P[kProjO].S, P[kProjO].wide, w[5]));
+      f.A = x.xn; f.W = w[6]; f.N = 2 * F; f.K = d; f.S = P[kProjGu].S; f.y = x.hbuf;
+      HIPTRY(sjd::launch_gemm_fused(sjd::kFusedSwiglu, f, s));
+      TRY(resid(x.hbuf, w[8], F, P[kProjDown].S, P[kProjDown].wide, l + 1 < c.n_layers ? x.lw[l + 1][0] : x.fnorm));
+      continue;
+    }
+    if (l > 0)  // (layer 0's input comes normed from launch_window_in)
+      HIPTRY(sjd::launch_resid_norm(x.x, x.rpart, pend, rplane, w[0], M, d, x.xn, x.mtiles, x.ss, nullptr, s));
+    sjd::GemmArgs g = normed;
+    g.A = x.xn; g.mtiles = x.mtiles; g.M = M; g.W = w[1]; g.N = Nqkv; g.K = d; g.S = P[kProjQkv].S;
+    g.wide = P[kProjQkv].wide; g.out = x.qkv; g.plane = qplane; g.ldo = Nqkv;
+    HIPTRY(sjd::launch_gemm(g, s));
+    HIPTRY(sjd::launch_rope_kv(x.qkv, P[kProjQkv].S, qplane, x.win, n_dev, n_host, M, H, Hkv, hd, x.rope, kv, x.cap_pad,
+                               sm, s));
     HIPTRY(sjd::launch_attention(a, hd, s));
     g = sjd::GemmArgs{};
     g.A = x.att; g.mtiles = x.mtiles; g.M = M; g.W = w[4]; g.N = d; g.K = Nq; g.S = P[kProjO].S;
     g.wide = P[kProjO].wide; g.out = x.rpart; g.plane = rplane; g.ldo = d;
     HIPTRY(sjd::launch_gemm(g, s));
-    HIPTRY(sjd::launch_resid_norm(x.x, x.rpart, P[kProjO].S, rplane, w[5], M, d, x.xn, x.mtiles, x.ss, s));
+    HIPTRY(sjd::launch_resid_norm(x.x, x.rpart, P[kProjO].S, rplane, w[5], M, d, x.xn, x.mtiles, x.ss, nullptr, s));
     g = normed;
     g.A = x.xn; g.mtiles = x.mtiles; g.M = M; g.W = w[6]; g.N = 2 * F; g.K = d; g.S = P[kProjGu].S;
     g.wide = P[kProjGu].wide; g.out = x.gup; g.plane = guplane; g.ldo = 2 * F;
@@ -209,10 +265,15 @@ int forward(Ctx& x, int M, const int32_t* n_dev, int n_host, float* logits, cons
     pend = P[kProjDown].S;
   }
   if (logits) {
-    HIPTRY(sjd::launch_resid_norm(x.x, x.rpart, pend, rplane, x.fnorm, M, d, x.xn, x.mtiles, x.ss, s));
     sjd::GemmArgs g = normed;
+    if (x.fused) {
+      g.ss = nullptr;
+      g.fours = x.fours;
+    } else {
+      HIPTRY(sjd::launch_resid_norm(x.x, x.rpart, pend, rplane, x.fnorm, M, d, x.xn, x.mtiles, x.ss, nullptr, s));
+    }
     g.A = x.xn; g.mtiles = x.mtiles; g.M = M; g.W = x.head; g.N = c.V; g.K = d; g.S = 1;
-    g.wide = 1;  // measured faster at 32 and 64 rows
+    g.wide = c.V >= kWideHeadV ? 1 : 0;
     g.out = logits; g.plane = 0; g.ldo = c.V;
     if (sm.mode == sjd::kStreamsMulti && sm.guided) {  // rows [32 b, 32 b + L): image b's guided logits
       g.cfg_rows = sm.L;
@@ -324,7 +385,7 @@ Ctx::Plan tune_projection(Ctx& x, int proj, const std::vector<Ctx::Plan>& cand, 
         g.A = x.att; g.mtiles = x.mtiles; g.W = w[4]; g.N = d; g.K = Nq;
         g.out = x.rpart; g.plane = rplane; g.ldo = d;
         if ((e = sjd::launch_gemm(g, s)) != hipSuccess) return e;
-        return sjd::launch_resid_norm(x.x, x.rpart, S, rplane, w[5], M, d, x.xn, x.mtiles, x.ss, s);
+        return sjd::launch_resid_norm(x.x, x.rpart, S, rplane, w[5], M, d, x.xn, x.mtiles, x.ss, nullptr, s);
       case kProjGu:
         g.W = w[6]; g.N = 2 * F; g.out = x.gup; g.plane = guplane; g.ldo = 2 * F;
         if ((e = sjd::launch_gemm(g, s)) != hipSuccess) return e;
@@ -333,7 +394,7 @@ Ctx::Plan tune_projection(Ctx& x, int proj, const std::vector<Ctx::Plan>& cand, 
         g.A = x.hbuf; g.mtiles = x.mtiles; g.W = w[8]; g.N = d; g.K = F;
         g.out = x.rpart; g.plane = rplane; g.ldo = d;
         if ((e = sjd::launch_gemm(g, s)) != hipSuccess) return e;
-        return sjd::launch_resid_norm(x.x, x.rpart, S, rplane, w[0], M, d, x.xn, x.mtiles, x.ss, s);
+        return sjd::launch_resid_norm(x.x, x.rpart, S, rplane, w[0], M, d, x.xn, x.mtiles, x.ss, nullptr, s);
     }
   };
   hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -439,6 +500,7 @@ extern "C" int sjd_init(const sjd_config* cfg, const sjd_weights* w, void* strea
   // weights: copied into library memory; matrices repacked into the GEMM
   // tile layout (bf16), fp32 inputs rounded to nearest even
   const int f32 = c.weights_f32 ? 1 : 0;
+  x.fused = fused_shape(c) && !(c.flags & SJD_TUNE);
   auto copy_rows = [&](const void* p, size_t count, const uint16_t** dst) -> int {
     uint16_t* b = nullptr;
     int rc = dalloc(x, &b, count);
@@ -453,9 +515,11 @@ extern "C" int sjd_init(const sjd_config* cfg, const sjd_weights* w, void* strea
   };
   // rows [row0, row0 + N) of src ([*][K]) as row blocks [nb0, nb0 + N/32) of
   // a tiled matrix of Ntot rows at dst
-  auto tile = [&](const void* p, size_t row0, int N, int K, uint16_t* dst, int Ntot, int nb0) -> int {
-    return sjd::launch_tile_weights(p, f32, row0, N, K, dst, Ntot / 32, nb0, s) == hipSuccess ? SJD_OK
-                                                                                             : SJD_EHIP;
+  // (pair: the projections of narrow models pair columns, see forward.h)
+  auto tile = [&](const void* p, size_t row0, int N, int K, uint16_t* dst, int Ntot, int nb0, int pair = 0) -> int {
+    return sjd::launch_tile_weights(p, f32, row0, N, K, dst, Ntot / 32, nb0, x.fused ? pair : 0, s) == hipSuccess
+               ? SJD_OK
+               : SJD_EHIP;
   };
   int rc = copy_rows(w->d_embed, (size_t)c.vocab_size * d, &x.embed);
   if (rc == SJD_OK) rc = copy_rows(w->d_final_norm, d, &x.fnorm);
@@ -475,14 +539,14 @@ extern "C" int sjd_init(const sjd_config* cfg, const sjd_weights* w, void* strea
     const size_t tq = (size_t)Nq * d, tkv = (size_t)Nkv * d;
     if (rc == SJD_OK) rc = dalloc(x, &qkv, tq + 2 * tkv);
     const int Nqkv = Nq + 2 * Nkv;
-    if (rc == SJD_OK) rc = tile(lp[1], 0, Nq, d, qkv, Nqkv, 0);
-    if (rc == SJD_OK) rc = tile(lp[2], 0, Nkv, d, qkv, Nqkv, Nq / 32);
-    if (rc == SJD_OK) rc = tile(lp[3], 0, Nkv, d, qkv, Nqkv, (Nq + Nkv) / 32);
+    if (rc == SJD_OK) rc = tile(lp[1], 0, Nq, d, qkv, Nqkv, 0, hd);
+    if (rc == SJD_OK) rc = tile(lp[2], 0, Nkv, d, qkv, Nqkv, Nq / 32, hd);
+    if (rc == SJD_OK) rc = tile(lp[3], 0, Nkv, d, qkv, Nqkv, (Nq + Nkv) / 32, hd);
     if (rc == SJD_OK) rc = dalloc(x, &wo, (size_t)d * Nq);
     if (rc == SJD_OK) rc = tile(lp[4], 0, d, Nq, wo, d, 0);
     if (rc == SJD_OK) rc = dalloc(x, &wgu, (size_t)2 * F * d);
-    if (rc == SJD_OK) rc = tile(lp[6], 0, F, d, wgu, 2 * F, 0);
-    if (rc == SJD_OK) rc = tile(lp[7], 0, F, d, wgu, 2 * F, F / 32);
+    if (rc == SJD_OK) rc = tile(lp[6], 0, F, d, wgu, 2 * F, 0, -1);
+    if (rc == SJD_OK) rc = tile(lp[7], 0, F, d, wgu, 2 * F, x.fused ? 0 : F / 32, -2);
     if (rc == SJD_OK) rc = dalloc(x, &wd, (size_t)d * F);
     if (rc == SJD_OK) rc = tile(lp[8], 0, d, F, wd, d, 0);
     o[1] = qkv; o[2] = nullptr; o[3] = nullptr; o[4] = wo; o[6] = wgu; o[7] = nullptr; o[8] = wd;
@@ -600,11 +664,17 @@ extern "C" int sjd_init(const sjd_config* cfg, const sjd_weights* w, void* strea
     }
   }
   const int sr = smax[1] > smax[3] ? smax[1] : smax[3];
-  if ((rc = dalloc(x, &x.qkv, (size_t)smax[0] * Mp * Nqkv)) ||
-      (rc = dalloc(x, &x.rpart, (size_t)sr * Mp * d)) ||
-      (rc = dalloc(x, &x.gup, (size_t)smax[2] * Mp * 2 * F)) ||
-      (rc = dalloc(x, &x.ss, (size_t)Mp * sjd::norm_chunks(d))))
+  const size_t nfours = (size_t)Mp * sjd::norm_chunks(d) * 64;
+  if (x.fused) {
+    if ((rc = dalloc(x, &x.fours, nfours)) || (rc = dalloc(x, &x.rpart, (size_t)sr * Mp * d))) return fail(rc);
+    // columns past d in the last chunk stay zero
+    if (hipMemsetAsync(x.fours, 0, nfours * sizeof(float), s) != hipSuccess) return fail(SJD_EHIP);
+  } else if ((rc = dalloc(x, &x.qkv, (size_t)smax[0] * Mp * Nqkv)) ||
+             (rc = dalloc(x, &x.rpart, (size_t)sr * Mp * d)) ||
+             (rc = dalloc(x, &x.gup, (size_t)smax[2] * Mp * 2 * F)) ||
+             (rc = dalloc(x, &x.ss, (size_t)Mp * sjd::norm_chunks(d)))) {
     return fail(rc);
+  }
   // zero the caches (rows past the fill are read, masked, by the attention
   // tiles), the window and the activation planes (pad rows stay finite)
   bool ok0 = true;
@@ -690,8 +760,7 @@ int prefill_stream(Ctx& x, const int32_t* d_prompt, int n, int cache, hipStream_
   const int P = Ctx::kPrefillRows;
   for (int start = 0; start < n - 1; start += P) {
     const int M = (n - 1 - start) < P ? (n - 1 - start) : P;
-    HIPTRY(sjd::launch_build_prefill(d_prompt, start, M, x.win, s));
-    TRY(forward(x, M, nullptr, start, nullptr, one, cache, s));
+    TRY(forward(x, M, d_prompt, nullptr, start, nullptr, one, cache, s));
   }
   return SJD_OK;
 }
@@ -730,8 +799,7 @@ int window_rows(const Ctx& x) { return 32 * (x.nstreams - 1) + x.c.L; }
 int step_forward(Ctx& x, int buf, float* logits, hipStream_t s) {
   const sjd::Streams sm = window_streams(x);
   auto enqueue = [&](hipStream_t q) -> int {
-    HIPTRY(sjd::launch_build_window(x.st, x.win, x.c.L, x.c.K, x.c.vis_lo, sm, q));
-    return forward(x, window_rows(x), &x.st->n, 0, logits, sm, 0, q);
+    return forward(x, window_rows(x), nullptr, &x.st->n, 0, logits, sm, 0, q);
   };
   if (!x.use_graph) return enqueue(s);
   if (!x.fwd_exec[buf]) {
@@ -894,8 +962,7 @@ extern "C" int sjd_forward_window(sjd_ctx* h, float* d_logits, void* stream) {
   TRY(cache_check(x));
   hipStream_t s = (hipStream_t)stream;
   const sjd::Streams sm = window_streams(x);
-  HIPTRY(sjd::launch_build_window(x.st, x.win, x.c.L, x.c.K, x.c.vis_lo, sm, s));
-  return forward(x, window_rows(x), &x.st->n, 0, d_logits, sm, 0, s);
+  return forward(x, window_rows(x), nullptr, &x.st->n, 0, d_logits, sm, 0, s);
 }
 
 extern "C" int sjd_get_plan(const sjd_ctx* h, int32_t* splits, int32_t n) {
@@ -907,8 +974,8 @@ extern "C" int sjd_get_plan(const sjd_ctx* h, int32_t* splits, int32_t n) {
       v[10 * cls + k] = x.plan[cls][k].S;
       v[10 * cls + 5 + k] = x.plan[cls][k].wide ? 8 : 4;
     }
-    v[10 * cls + 4] = 1;  // LM head: unsplit, 8 column blocks per workgroup
-    v[10 * cls + 9] = 8;
+    v[10 * cls + 4] = 1;  // LM head: unsplit
+    v[10 * cls + 9] = x.c.V >= kWideHeadV ? 8 : 4;
   }
   for (int i = 0; i < n && i < 20; ++i) splits[i] = v[i];
   return SJD_OK;

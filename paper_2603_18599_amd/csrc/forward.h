@@ -6,6 +6,7 @@
 namespace sjd {
 
 constexpr int kGemmMaxSplits = 32;
+constexpr int kFusedMaxChunks = 4;  // narrow models (fused.hip): 256-column norm chunks, d <= 1024
 
 // Weights are repacked at init into 32-row x 64-column tiles (4 KB, bf16):
 // tile (nb, kb) of a [N][K] matrix starts at element (kb * (N/32) + nb) *
@@ -44,6 +45,7 @@ struct GemmArgs {
   // inv_d + eps) multiplies the row of the product before the store
   const float* ss;
   int ss_n;
+  const float* fours;  // or (ss NULL, narrow models): sums of squares of each four columns, [row][ss_n * 64]
   float inv_d, eps;
   // guided head (M > 32 only): for each image b (product rows [64 b, 64 b +
   // 64)), output row 32 b + m (m < cfg_rows) is u + cfg_w (c - u) with c =
@@ -60,10 +62,16 @@ int gemm_splits(int N, int K, int target_wgs, bool wide);
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s);
 
 // Repacks rows [row0, row0 + N) of a row-major [*][K] bf16 (or fp32, then
-// rounded to nearest even) matrix into the tile layout above, as row blocks
-// [nb0, nb0 + N/32) of a tiled matrix of nblk_total row blocks at dst.
+// rounded to nearest even) matrix into the tile layout above. Plain (pair 0):
+// row blocks [nb0, nb0 + N/32) of a tiled matrix of nblk_total row blocks at
+// dst. Paired, for the projections of narrow models (fused.hip):
+//  - pair > 0 (q, k, v; pair = hd): row r of head r / hd, dim j = r % hd, goes to
+//    row block nb0 + r / hd * (hd / 32) + (j % (hd / 2)) / 16, row j % 16, + 16 for
+//    the upper half of the dims;
+//  - pair < 0 (-1 gate, -2 up): row r goes to row block nb0 + r / 16, row r % 16, +
+//    16 for up.
 hipError_t launch_tile_weights(const void* src, int is_f32, size_t row0, int N, int K, uint16_t* dst,
-                               int nblk_total, int nb0, hipStream_t s);
+                               int nblk_total, int nb0, int pair, hipStream_t s);
 
 // Window description in device memory (written by the window builder).
 // Row a's ancestors: bit i = row base + i of its own stream (base 0 for
@@ -157,22 +165,43 @@ struct AttnArgs {
   int nsplit_max;
   uint16_t* out;         // tiled activations (act_off), `mtiles` row tiles
   int mtiles;
+  int whole;             // 64-dim heads, at most kWholeChunks chunks of capacity: one kernel
   int qparts;            // workgroups per key / value head, each taking H / Hkv / qparts query heads
 };
 constexpr int kAttnChunk = 128;  // keys per workgroup (4 waves x 32)
+constexpr int kWholeChunks = 4;  // k_attn_whole: chunks of a cache, at most (and no more than kCombGroup)
 hipError_t launch_attention(const AttnArgs& a, int hd, hipStream_t s);
 
 // elementwise kernels
-// ids outside [0, vocab) are read as token fallback (in [0, vocab))
-hipError_t launch_embed(const uint16_t* E, const Window* win, int M, int d, int vocab, int fallback, float* x,
-                        hipStream_t s);
+// A window's rows and their embedding, ready for the first layer: window tokens,
+// positions and ancestors (from the decoder state, or from a prompt), x = E[tok]
+// (ids outside [0, vocab) read as vis_lo), y = x * g as tiled activations and the
+// norm's sums of squares (chunks ss, or for narrow models fours).
+struct WindowIn {
+  const DevState* st;     // state of image 0, or NULL:
+  const int32_t* prompt;  //   rows are prompt[start ..) at positions start ..
+  int start;
+  int M, L, K, vis_lo;
+  Streams sm;
+  Window* win;
+  const uint16_t* E;
+  int d, vocab;
+  float* x;
+  const uint16_t* g;
+  uint16_t* y;
+  int mtiles;
+  float* ss;
+  float* fours;
+};
+hipError_t launch_window_in(const WindowIn& a, hipStream_t s);
 // RMSNorm split in two: x += sum of S fp32 partial planes (fixed order; S
 // may be 0), y = x * g as tiled activations (mtiles row tiles) and the sums of
 // squares of x over 256-element chunks, ss[m][c] (c < norm_chunks(d)); the GEMM
-// that consumes y applies the row scale 1 / sqrt(mean(x^2) + eps).
+// that consumes y applies the row scale 1 / sqrt(mean(x^2) + eps). With fours
+// (narrow models) the sums of each four columns go there instead.
 inline int norm_chunks(int d) { return (d + 255) / 256; }
 hipError_t launch_resid_norm(float* x, const float* part, int S, size_t plane, const uint16_t* g, int M, int d,
-                             uint16_t* y, int mtiles, float* ss, hipStream_t s);
+                             uint16_t* y, int mtiles, float* ss, float* fours, hipStream_t s);
 // rotary embedding of q and k, key row and transposed value column into the caches
 struct KvPlanes {
   uint16_t *q, *q_lo, *kc, *kc_lo, *vt, *vt_lo;
@@ -186,5 +215,33 @@ hipError_t launch_rope_kv(const float* qkv, int S, size_t plane, const Window* w
 // planes at columns [0, F), up = at columns [F, 2F) (row stride 2F)
 hipError_t launch_swiglu(const float* P, int S, size_t plane, int M, int F, uint16_t* h, int mtiles, hipStream_t s);
 hipError_t launch_f32_to_bf16(const float* src, uint16_t* dst, size_t n, hipStream_t s);
+
+// ---- narrow models (fused.hip): one kernel per projection
+enum { kFusedRope = 0, kFusedResid = 1, kFusedSwiglu = 2 };
+struct FusedArgs {
+  const uint16_t* A;  // tiled activations, mtiles row tiles
+  int mtiles, M;
+  const uint16_t* W;  // tiled weights (q, k, v and gate | up paired)
+  int N, K, S;        // S: the plan's split of K, which sets the summation order
+  // norm scale of the input (Rope, Swiglu): sums of squares of each four
+  // columns, [rows][nch * 64]
+  const float* fours;
+  int nch;
+  float inv_d, eps;
+  // Resid: x += product; y = x * g as tiled activations, fours of x
+  float* x;
+  const uint16_t* g;
+  uint16_t* y;  // (Swiglu: the output)
+  float* fours_out;
+  int nch_out;
+  // Rope
+  const Window* win;
+  const int32_t* n_dev;
+  int n_host, H, Hkv, hd, cap;
+  const float2* rope;
+  KvPlanes kv;
+  Streams st;
+};
+hipError_t launch_gemm_fused(int epi, const FusedArgs& a, hipStream_t s);
 
 }  // namespace sjd

@@ -55,12 +55,13 @@ constexpr int kSsRegs = 16;
 
 SJD_DEV bf16x8 as_bf16x8(const u32x4& u) { return __builtin_bit_cast(bf16x8, u); }
 
-template <int MT>
+template <int MT, bool FOURS>
 struct GemmSmem {
   // [buffer][row tile][hi / lo][16-byte chunk][lane]: A tiles in MFMA operand
   // order, as in memory
   u32x4 a[2][MT][2][4][kWave];
   float inv[32 * MT];
+  float chunk[FOURS ? 32 * MT : 1][kFusedMaxChunks];
 };
 
 // The main loop is straight-line code: vector loads return in issue order
@@ -87,9 +88,11 @@ SJD_DEV void gemm_tile_of(int id, int groups, int splits, int& group, int& split
   group = lin % groups;
 }
 
-template <int kRing, int MT, int NW>
+// FOURS: the RMS scale comes from fours (narrow models' LM head); a variant of
+// its own, for its sums take 64 registers.
+template <int kRing, int MT, int NW, bool FOURS = false>
 __global__ __launch_bounds__(NW * kWave) void k_gemm(GemmArgs g) {
-  __shared__ GemmSmem<MT> sm;
+  __shared__ GemmSmem<MT, FOURS> sm;
   const int wave = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
   const int r32 = lane & 31, half = lane >> 5;
   const int T = g.K / 64, nblk = g.N / 32;
@@ -105,7 +108,7 @@ __global__ __launch_bounds__(NW * kWave) void k_gemm(GemmArgs g) {
   // fused RMSNorm: row scale from the chunk sums of squares. The loads go
   // into registers ahead of the weight stream and are summed after it (a sum
   // here would wait for them before the first weight load is issued).
-  const bool has_ss = g.ss != nullptr && (int)threadIdx.x < 32 * MT;
+  const bool has_ss = !FOURS && g.ss != nullptr && (int)threadIdx.x < 32 * MT;
   const float* ssr = has_ss ? g.ss + (size_t)((int)threadIdx.x < g.M ? threadIdx.x : 0) * g.ss_n : nullptr;
   float ssv[kSsRegs];
   if (has_ss)
@@ -171,14 +174,21 @@ __global__ __launch_bounds__(NW * kWave) void k_gemm(GemmArgs g) {
     }
   }
 
+  if constexpr (FOURS) {  // the norm's chunk sums from its fours
+    for (int p = threadIdx.x; p < 32 * MT * g.ss_n; p += NW * kWave)
+      sm.chunk[p / g.ss_n][p % g.ss_n] = butterfly64(g.fours + (size_t)p * 64);
+    __syncthreads();
+  }
   if (threadIdx.x < 32 * MT) {
     float ssum = 0.0f;
-    if (has_ss) {
+    if constexpr (FOURS) {
+      for (int c = 0; c < g.ss_n; ++c) ssum += sm.chunk[threadIdx.x][c];
+    } else if (has_ss) {
 #pragma unroll
       for (int c = 0; c < kSsRegs; ++c) ssum += c < g.ss_n ? ssv[c] : 0.0f;
       for (int c = kSsRegs; c < g.ss_n; ++c) ssum += ssr[c];
     }
-    sm.inv[threadIdx.x] = has_ss ? rsqrtf(ssum * g.inv_d + g.eps) : 1.0f;
+    sm.inv[threadIdx.x] = FOURS || has_ss ? rsqrtf(ssum * g.inv_d + g.eps) : 1.0f;
   }
   __syncthreads();
   if (!active) return;
@@ -240,13 +250,29 @@ int gemm_splits(int N, int K, int target_wgs, bool wide) {
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
   if (g.M < 1 || g.M > 128 || g.M > 32 * g.mtiles || g.N % 32 || g.K % 64 || g.S < 1 || g.S > kGemmMaxSplits) return hipErrorInvalidValue;
   const int MT = (g.M + 31) / 32;
+  if (g.fours && (g.ss || g.ss_n > kFusedMaxChunks)) return hipErrorInvalidValue;
   if (g.cfg_rows < 0 || g.cfg_rows > 32 || (g.cfg_rows > 0 && (MT & 1))) return hipErrorInvalidValue;
   const int nw = g.wide ? kGWavesWide : kGWaves;
   const dim3 grid((unsigned)(((g.N / 32 + nw - 1) / nw) * g.S)), block((unsigned)(nw * kWave));
   // at one workgroup per compute unit or fewer nothing else hides a
   // workgroup's load latency: keep more weight tiles in flight
   const bool lone = grid.x <= 256;
-  if (g.wide) {
+  if (g.fours && !g.wide && MT == 1) {
+    hipLaunchKernelGGL((k_gemm<kRingDeep, 1, kGWaves, true>), grid, block, 0, s, g);
+  } else if (g.fours && !g.wide) {
+    switch (MT) {
+      case 2: hipLaunchKernelGGL((k_gemm<kRingDepth, 2, kGWaves, true>), grid, block, 0, s, g); break;
+      case 3: hipLaunchKernelGGL((k_gemm<kRingDepth, 3, kGWaves, true>), grid, block, 0, s, g); break;
+      default: hipLaunchKernelGGL((k_gemm<kRingDepth, 4, kGWaves, true>), grid, block, 0, s, g); break;
+    }
+  } else if (g.fours) {
+    switch (MT) {
+      case 1: hipLaunchKernelGGL((k_gemm<kRingDepth, 1, kGWavesWide, true>), grid, block, 0, s, g); break;
+      case 2: hipLaunchKernelGGL((k_gemm<kRingDepth, 2, kGWavesWide, true>), grid, block, 0, s, g); break;
+      case 3: hipLaunchKernelGGL((k_gemm<kRingDepth, 3, kGWavesWide, true>), grid, block, 0, s, g); break;
+      default: hipLaunchKernelGGL((k_gemm<kRingDepth, 4, kGWavesWide, true>), grid, block, 0, s, g); break;
+    }
+  } else if (g.wide) {
     switch (MT) {
       case 1: hipLaunchKernelGGL((k_gemm<kRingDepth, 1, kGWavesWide>), grid, block, 0, s, g); break;
       case 2: hipLaunchKernelGGL((k_gemm<kRingDepth, 2, kGWavesWide>), grid, block, 0, s, g); break;

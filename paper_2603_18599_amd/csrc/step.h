@@ -6,9 +6,6 @@
 #include "forward.h"
 
 namespace sjd {
-hipError_t launch_build_window(const DevState* st, Window* w, int L, int K, int vis_lo, const Streams& sm,
-                               hipStream_t s);
-hipError_t launch_build_prefill(const int32_t* prompt, int start, int M, Window* w, hipStream_t s);
 // next window from caller drafts: chain of tok[0..L) (row j's draft), row j's
 // draft distribution from row j of the draft logits when has_q
 // adds the count of NaN / +inf entries of p[0 .. n) to *cnt (zeroed first when reset)

@@ -1,62 +1,11 @@
-// Step bookkeeping kernels: window layout from the device state, prefill
-// windows, state initialisation, KV commit (moving an accepted sibling's
+// Step bookkeeping kernels: state initialisation, KV commit (moving an accepted sibling's
 // key/value row) and the state update after verification. Everything stays
 // in device memory; the host only enqueues.
-//
-// Window layout (the paper fixes L verified positions per forward, Sec. 3.3,
-// and K candidates at each of the first D positions after a rejection,
-// Sec. 4.1): slot 0 holds the pending token (last committed, not yet cached)
-// at position n; slot i, 1 <= i < n_s, holds spine draft i-1 at n + i;
-// slot n_s + d(K-1) + k-2 holds sibling k of depth d at n + 1 + d and sees
-// slots 0..d and itself. A missing sibling slot is fed token vis_lo.
 #include "device.h"
 #include "forward.h"
 #include "step.h"
 
 namespace sjd {
-
-__global__ void k_build_window(const DevState* st, Window* w, int L, int K, int vis_lo, Streams sm) {
-  const int a = threadIdx.x;
-  const bool multi = sm.mode != kStreamsOne;
-  const int z = multi ? a >> 5 : 0;      // stream of this row
-  const int loc = multi ? (a & 31) : a;  // window row within its stream
-  if (loc >= L) {  // padding row of a multi-stream window: never read, never cached
-    if (multi) {
-      w->tok[a] = vis_lo;
-      w->pos[a] = st->n;
-      w->anc[a] = 0ull;
-    }
-    return;
-  }
-  // batched: stream z is image z; guided: streams 2b, 2b + 1 are image b
-  const DevState* d = multi ? st + stream_image(sm, z) : st;
-  const bool unc = multi && stream_uncond(sm, z);
-  const int n = d->n, n_s = d->n_s;
-  int tok, pos;
-  uint64_t anc;
-  if (loc < n_s) {
-    tok = loc == 0 ? (unc ? d->pending_u : d->pending) : d->spine[loc - 1];
-    pos = n + loc;
-    anc = loc == 63 ? ~0ull : ((1ull << (loc + 1)) - 1ull);
-  } else {
-    const int t = loc - n_s, dd = t / (K - 1), k = t % (K - 1);
-    const int y = d->sib[dd * (K - 1) + k];
-    tok = y >= 0 ? y : vis_lo;
-    pos = n + 1 + dd;
-    anc = ((1ull << (dd + 1)) - 1ull) | (1ull << loc);
-  }
-  w->tok[a] = tok;
-  w->pos[a] = unc ? pos + d->delta_u : pos;
-  w->anc[a] = anc;
-}
-
-__global__ void k_build_prefill(const int32_t* prompt, int start, int M, Window* w) {
-  const int a = threadIdx.x;
-  if (a >= M) return;
-  w->tok[a] = prompt[start + a];
-  w->pos[a] = start + a;
-  w->anc[a] = a == 63 ? ~0ull : ((1ull << (a + 1)) - 1ull);
-}
 
 // Placeholders of the first window: uniform over the support (stream tag 6,
 // trial 0, step word 0xFFFFFFFF, row = window index), the row end token at
@@ -200,17 +149,6 @@ hipError_t launch_set_drafts(DevState* st, const int32_t* tok, int L, bool has_q
   return hipGetLastError();
 }
 
-hipError_t launch_build_window(const DevState* st, Window* w, int L, int K, int vis_lo, const Streams& sm,
-                               hipStream_t s) {
-  const bool multi = sm.mode != kStreamsOne;
-  if (multi && (sm.nz < 1 || sm.nz > kMaxStreams || L > 32)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_build_window, dim3(1), dim3(multi ? 32 * sm.nz : 64), 0, s, st, w, L, K, vis_lo, sm);
-  return hipGetLastError();
-}
-hipError_t launch_build_prefill(const int32_t* prompt, int start, int M, Window* w, hipStream_t s) {
-  hipLaunchKernelGGL(k_build_prefill, dim3(1), dim3(64), 0, s, prompt, start, M, w);
-  return hipGetLastError();
-}
 hipError_t launch_state_init(DevState* st, const int32_t* prompt, int n_p, const int32_t* uncond, int n_u, int L,
                              int V, int vis_lo, int eol, int row_len, uint64_t seed, hipStream_t s) {
   hipLaunchKernelGGL(k_state_init, dim3(1), dim3(64), 0, s, st, prompt, n_p, uncond, n_u, L, V, vis_lo, eol, row_len,

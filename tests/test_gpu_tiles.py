@@ -42,3 +42,53 @@ def test_window_forward_at_tile_edges(orc, over):
     print(f"max |logit error| = {err:.3e}, max |logit| = {np.abs(ref).max():.3f}", flush=True)
     assert np.isfinite(got).all()
     assert err <= np.abs(ref).max() * 2.0 ** -11, err
+
+
+# Narrow models run each projection with its consumer as one kernel, wider ones
+# (and SJD_TUNE contexts, whose timed candidates are the split kernels) as two;
+# short caches of 64-dim heads take the one-kernel attention. Under one plan the
+# results have the same bits. Shapes: more splits than k-steps, uneven splits, a
+# projection too long for one kernel, 128-dim heads, grouped heads, one to four
+# streams, prompts of one and of several prefill windows, window rows past a
+# 32-row tile, caches of more chunks than the one-kernel attention takes.
+NARROW = [
+    (dict(d_model=64, n_heads=1, n_kv_heads=1, ffn_dim=64, L=1, K=1, D=0, n_prompt=3), "2,5,3,1"),
+    (dict(d_model=320, n_heads=5, n_kv_heads=1, ffn_dim=1600, L=9, K=2, D=2, n_prompt=33), "4,1,5,22"),
+    (dict(d_model=576, n_heads=6, n_kv_heads=2, head_dim=128, ffn_dim=1536, L=33, K=4, D=3, n_prompt=97), "8,7,3,9"),
+    (dict(d_model=960, n_heads=15, n_kv_heads=15, ffn_dim=2816, L=32, K=4, D=3, n_prompt=64, batch=4), "8,8,5,22"),
+    (dict(d_model=512, n_heads=8, n_kv_heads=4, ffn_dim=1024, L=20, K=4, D=3, n_prompt=200, cfg_w=3.0), "3,32,17,31"),
+    (dict(d_model=256, n_heads=4, n_kv_heads=4, ffn_dim=1024, L=64, K=4, D=3, n_prompt=470, max_seq=1000), "2,2,2,4"),
+]
+
+
+@pytest.mark.parametrize("over,plan", NARROW, ids=[f"d{o['d_model']}-L{o['L']}" for o, _ in NARROW])
+def test_narrow_models_match_the_split_kernels_bitwise(monkeypatch, over, plan):
+    from paper_2603_18599_amd.sjd import SJD_AC, SJD_PD, SJD_TUNE
+    monkeypatch.setenv("SJD_SPLITS", plan)
+    # (shapes without a recorded plan: windows of more than 32 rows take the closed
+    # form on both sides)
+    base = model_config("tiny", weights_f32=False, vocab_size=1056, V=1056, **over)
+    w, prompt = setup(base, wseed=31, pseed=32, device="cuda")
+    dev = weights_device(w)
+    B, L = base.get("batch", 1), base["L"]
+    got = []
+    for flags in (SJD_AC | SJD_PD, SJD_AC | SJD_PD | SJD_TUNE):
+        print(f"case {over} flags {flags}", flush=True)
+        eng = make_engine(dict(base, flags=flags), dev)
+        for b in range(B):
+            p = prompt[:len(prompt) - b].cuda()
+            if base.get("cfg_w"):
+                eng.prefill_cfg(p, p[7:].contiguous(), 5, image=b)
+            else:
+                eng.prefill_image(b, p, 5 + b)
+        logits = torch.zeros(32 * (B - 1) + L, base["V"], device="cuda")
+        metas = torch.zeros(2, B, 8, dtype=torch.int32, device="cuda")
+        for t in range(2):
+            eng.step(1.0, 200, 5, t, out_meta=metas[t])
+        eng.forward_window(logits)
+        torch.cuda.synchronize()
+        got.append((logits.cpu(), metas.cpu()))
+        eng.close()
+    assert torch.equal(got[0][1], got[1][1])
+    for b in range(B):
+        assert torch.equal(got[0][0][32 * b:32 * b + L], got[1][0][32 * b:32 * b + L])
