@@ -10,6 +10,10 @@ constexpr uint32_t kFlagPD = 2u;
 constexpr uint32_t kFlagPDInline = 1u << 30;  // (internal) rows draw their own drafting candidates
 constexpr long kPdInlineRows = 512;           // launches of at most this many rows do
 constexpr uint32_t kFlagFullSelect = 1u << 29;  // (internal) every row takes the full-row selection
+constexpr uint32_t kFlagDraftStats = 1u << 28;  // (internal) draft statistics are in the rows' records
+// Launches of at most this many rows hold target and draft row of a window row
+// in one workgroup (see launch_verify)
+constexpr long two_row_rows(int V) { return V > 4096 && V <= 16384 ? 1280 : 512; }
 constexpr int kRecInts = 16;  // per-row record: tok, stage, 7 drafting candidates, fresh, pad
 constexpr int kVerifyMaxV = 65536;  // logits per row held on chip
 constexpr int kVerifyMaxK = 2048;   // kept (top-k) tokens per row when V > kVerifyMaxK

@@ -4,23 +4,19 @@
 // k_verify_rows: one workgroup per (trial, row). The row is read once,
 // coalesced (float4 per thread), into registers. Every full-row pass is kept
 // to a few instructions per logit; the exponentials, normalisers and all
-// decisions run over the compact list of kept tokens (at most 2048):
-//  - top-k selection: one histogram over bins of the row's [min, max] range
-//    (well spread for real logits, so the LDS atomics rarely collide); one
-//    pass then marks every entry of a bin above the threshold bin in a
-//    bitmap of the kept set and collects the threshold bin's entries, whose
-//    exact (value desc, index asc) rank decides which of them join it; a
-//    radix select over order-preserving keys is the fallback for degenerate
-//    rows (many equal values);
-//  - compaction: per-word prefix popcounts of the bitmap give each kept token
-//    its rank, which indexes the compact arrays and the random stream (four
-//    consecutive ranks share one Philox block);
-//  - the draft row (when the row has a draft distribution) goes through the
-//    same selection into a second bitmap; one pass stores its logits at the
-//    target's kept entries and at its own kept entries (for its normaliser);
-//  - accept tests, residual draws (Theorem 2's recursion for several
-//    candidates), drafting candidates and bonus draws run over the compact
-//    list only.
+// decisions run over the entries near or above the top-k threshold:
+//  - top-k selection by candidates (fast_select): a sample of the row bounds the
+//    threshold from below, one pass appends the entries that reach it to LDS,
+//    and the exact threshold and normaliser come from those alone;
+//  - rows that the candidates cannot decide are selected whole: a histogram over
+//    the row's range (radix select for degenerate rows), a bitmap of the kept
+//    set, prefix popcounts;
+//  - a row that draws gets the compact list of its kept tokens (index order: the
+//    rank indexes the random stream, four consecutive ranks share one Philox
+//    block); residual draws (Theorem 2's recursion for several candidates),
+//    drafting candidates and bonus draws run over it;
+//  - the draft row's statistics come from the same workgroup (small launches:
+//    both rows in registers), from k_draft_stats, or from the previous step.
 // k_verify_finalize: one wave per trial. Finds the first rejected spine row,
 // the committed tokens, and assembles the next window.
 //
@@ -54,13 +50,14 @@ constexpr int kSampBins = 512;   // candidate-path sample histogram (bins over t
 
 // Compact list of a row's kept tokens, by rank (index order).
 struct SpList {
-  uint16_t x[kKcap];  // token index,
-  float p[kKcap];     //   target probability,
-  float q[kKcap];     //   draft probability
+  float p[kKcap];  // target probability (the token index is in VSh::hx.x),
+  float q[kKcap];  //   draft probability
 };
 
-template <int BLOCK, int NC>
+// TWO: the workgroup holds the target row and its draft row together.
+template <int BLOCK, int NC, bool TWO>
 struct VSh {
+  static constexpr int R = TWO ? 2 : 1;
   static constexpr int W = BLOCK / kWave;
   static constexpr int NW = BLOCK * NC / 8;  // bitmap words (32 entries each)
   // candidate path: entries of a row at or above its estimated threshold,
@@ -76,32 +73,35 @@ struct VSh {
       uint32_t hist[kBins];
       float qc[kKcap];  // draft row's kept weights (its normaliser)
     };
-    uint32_t hist_q[kBins];  // the draft row's histogram when both rows are selected together
+    uint32_t hist_q[TWO ? kBins : 1];  // the draft row's histogram when both rows are selected together
     // per selected row (target, draft): threshold-bin entries, then sentinels
     // that outrank nothing (-inf, INT_MAX)
-    float cand_v[2][kCandCap + 8];
-    int cand_x[2][kCandCap + 8];
+    float cand_v[R][kCandCap + 8];
+    int cand_x[R][kCandCap + 8];
   };
   // scratch of the candidate path
   struct FastSel {
     float cv[CAP];    // target candidates: logit (after the normaliser: weight, or -1 if not kept)
-    float cq[CAP];    //   the draft logit of the same token
-    int32_t cx[CAP];  //   token index
-    uint32_t hist[2][kFastBins];
-    float tb_v[2][kCandCap + 8];  // threshold-bin entries, then sentinels
-    int tb_x[2][kCandCap + 8];
+    float cq[TWO ? CAP : 1];  //   the draft logit of the same token
+    int32_t cx[CAP];          //   token index
+    float tb_v[R][kCandCap + 8];  // threshold-bin entries, then sentinels
+    int tb_x[R][kCandCap + 8];
     int tb_s[1][kCandCap + 8];  // the target's threshold-bin entries' candidate slots
   };
   uint32_t bm[NW];    // kept set of the target row
   int32_t pre[NW];    // its per-word prefix popcounts
   union {
     SpList sp;        // compact list of the target row's kept tokens
-    float dv[CAP];    // candidate path: the draft row's candidates (dead before the list is built)
+    float dv[TWO ? CAP : 1];  // candidate path: the draft row's candidates (dead before the list is built)
   } u;
   union {
     OldSel o;
     FastSel f;
   };
+  union {
+    uint32_t hist[R][kFastBins];  // candidate path: histograms (dead before the list is built)
+    uint16_t x[kKcap];            // token indices of the compact list
+  } hx;
   uint64_t pd_w[W * 8];  // per-wave drafting keys
   int pd_o[8];            // the drafting draws
   double red_d[2 * W];
@@ -112,6 +112,34 @@ struct VSh {
   int tau_x[2], bin[2], above[2], ncand[2];
   int wcnt[2][W];  // candidate path: candidates per wave (-1: overflow)
   int fflag;       // candidate path: a row needs the full selection
+  int dec;         // the row's first draft is accepted and nothing is left to draw
+};
+// What fast_select alone needs (k_draft_stats): a third of VSh, so that the
+// workgroups of a compute unit are bounded by their registers.
+template <int BLOCK, int NC>
+struct DSh {
+  static constexpr int W = BLOCK / kWave;
+  static constexpr int CAP = VSh<BLOCK, NC, false>::CAP, CAPW = VSh<BLOCK, NC, false>::CAPW;
+  // (as a draft row: values without token indices, see fast_select)
+  struct {
+    float cv[1], cq[1];
+    int32_t cx[1];
+    float tb_v[2][kCandCap + 8];
+    int tb_x[2][kCandCap + 8];
+    int tb_s[1][1];
+  } f;
+  union {
+    float dv[CAP];
+  } u;
+  union {
+    uint32_t hist[2][kFastBins];
+  } hx;
+  double red_d[2 * W];
+  alignas(16) float red_f[8 * W];
+  float tau_v[2];
+  int tau_x[2], bin[2], above[2], ncand[2];
+  int wcnt[2][W];
+  int fflag;
 };
 static_assert(kBins == kKcap, "the draft weights reuse the histogram");
 
@@ -216,23 +244,34 @@ struct RowStats {
   }
 };
 
+// Register slots that every row of a launch shape fills (launch_verify's ranges
+// of V): their lanes need no test.
+template <int BLOCK, int NC>
+constexpr int kFullSlots = NC == 16 ? 8 : BLOCK == 1024 ? 4 : BLOCK == 512 ? 2 : 0;
+
 // The row in registers: chunk c = tid + i * BLOCK holds entries 4c .. 4c+3.
 template <int BLOCK, int NC>
 SJD_DEV void load_row(float4 (&v)[NC], const float* row, int V) {
   const float4* g = (const float4*)row;
   const int nchunk = V >> 2;
+  // (uniform branches: only the row's last register slot needs a lane mask)
 #pragma unroll
   for (int i = 0; i < NC; ++i) {
     const int c = threadIdx.x + i * BLOCK;
-    v[i] = c < nchunk ? g[c] : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+    if (i < kFullSlots<BLOCK, NC> || (i + 1) * BLOCK <= nchunk) {
+      v[i] = g[c];
+    } else {
+      v[i] = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+      if (c < nchunk) v[i] = g[c];
+    }
   }
 }
 
 // Radix select (fallback): k-th largest by (value desc, index asc) over
 // order-preserving keys (11 + 11 + 10 bits), then over the indices of the
 // entries tied at the threshold key (11 + 11 bits).
-template <int BLOCK, int NC>
-SJD_DEV void radix_topk(const float4 (&v)[NC], int V, int k, VSh<BLOCK, NC>& sh, float& tau_v, int& tau_x) {
+template <int BLOCK, int NC, class Sh>
+SJD_DEV void radix_topk(const float4 (&v)[NC], int V, int k, Sh& sh, float& tau_v, int& tau_x) {
   constexpr int W = BLOCK / kWave;
   const int tid = threadIdx.x;
   const int nchunk = V >> 2;
@@ -337,8 +376,8 @@ SJD_DEV void radix_topk(const float4 (&v)[NC], int V, int k, VSh<BLOCK, NC>& sh,
 
 // Block-wide largest value of the row in registers and its smallest value
 // above -inf.
-template <int BLOCK, int NC>
-SJD_DEV void row_maxmin(const float4 (&v)[NC], VSh<BLOCK, NC>& sh, float& mx, float& mn) {
+template <int BLOCK, int NC, class Sh>
+SJD_DEV void row_maxmin(const float4 (&v)[NC], Sh& sh, float& mx, float& mn) {
   constexpr int W = BLOCK / kWave;
   mx = -INFINITY;
   mn = INFINITY;
@@ -389,11 +428,11 @@ SJD_DEV void bitmap_from_tau(const float4 (&v)[NC], int V, const RowStats& st, u
 // kept set and its prefix popcounts pre, sets st.all / tau_v / tau_x (the
 // k-th kept entry: kept = l > tau_v or (l == tau_v and x <= tau_x)) and
 // returns the number of kept entries.
-template <int BLOCK, int NC>
-SJD_DEV int select_kept(const float4 (&v)[NC], int V, int top_k, float mx, float mn, VSh<BLOCK, NC>& sh,
+template <int BLOCK, int NC, class Sh>
+SJD_DEV int select_kept(const float4 (&v)[NC], int V, int top_k, float mx, float mn, Sh& sh,
                         uint32_t* bm, int32_t* pre, RowStats& st) {
   constexpr int W = BLOCK / kWave;
-  constexpr int NW = VSh<BLOCK, NC>::NW;
+  constexpr int NW = Sh::NW;
   const int tid = threadIdx.x;
   const int nchunk = V >> 2;
   const int k = (top_k <= 0 || top_k >= V) ? V : top_k;
@@ -645,8 +684,8 @@ SJD_DEV void block_sum_d2(double& a, double& b, double* red) {
 }
 
 // Largest value and smallest value above -inf of both rows.
-template <int BLOCK, int NC>
-SJD_DEV void row_maxmin2(const float4 (&v)[NC], const float4 (&u)[NC], VSh<BLOCK, NC>& sh, float (&mx)[2],
+template <int BLOCK, int NC, class Sh>
+SJD_DEV void row_maxmin2(const float4 (&v)[NC], const float4 (&u)[NC], Sh& sh, float (&mx)[2],
                          float (&mn)[2]) {
   constexpr int W = BLOCK / kWave;
   mx[0] = mx[1] = -INFINITY;
@@ -680,12 +719,12 @@ SJD_DEV void row_maxmin2(const float4 (&v)[NC], const float4 (&u)[NC], VSh<BLOCK
 // nothing decided, when either row needs the one-row path (every entry kept,
 // a degenerate value range, or more than kCandCap entries in a threshold
 // bin); the decision is uniform over the workgroup.
-template <int BLOCK, int NC>
+template <int BLOCK, int NC, class Sh>
 SJD_DEV bool select_kept2(const float4 (&v)[NC], const float4 (&u)[NC], int V, int top_k, const float (&mx)[2],
-                          const float (&mn)[2], VSh<BLOCK, NC>& sh, RowStats& ps, RowStats& qs, int& nk,
+                          const float (&mn)[2], Sh& sh, RowStats& ps, RowStats& qs, int& nk,
                           int& nq) {
   constexpr int W = BLOCK / kWave;
-  constexpr int NW = VSh<BLOCK, NC>::NW;
+  constexpr int NW = Sh::NW;
   const int tid = threadIdx.x;
   const int nchunk = V >> 2;
   const int k = (top_k <= 0 || top_k >= V) ? V : top_k;
@@ -883,24 +922,22 @@ SJD_DEV float wave_vmax_dpp(float v) {
   return wave_reduce32(v, [](float a, float b) { return __builtin_elementwise_maximum(a, b); });
 }
 
-// Block-wide max of four values; every thread gets the four results.
-template <int W>
-SJD_DEV void block_max4(float (&a)[4], float* red) {
+// Block-wide max of N (2 or 4) values; every thread gets the results.
+template <int W, int N>
+SJD_DEV void block_max_n(float (&a)[N], float* red) {
   const int w = threadIdx.x / kWave;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) a[i] = wave_vmax_dpp(a[i]);
-  if ((threadIdx.x & (kWave - 1)) == 0) *(float4*)&red[4 * w] = make_float4(a[0], a[1], a[2], a[3]);
+  for (int i = 0; i < N; ++i) a[i] = wave_vmax_dpp(a[i]);
+  if ((threadIdx.x & (kWave - 1)) == 0)
+#pragma unroll
+    for (int i = 0; i < N; ++i) red[N * w + i] = a[i];
   __syncthreads();
-  float4 m = *(const float4*)&red[0];
+#pragma unroll
+  for (int i = 0; i < N; ++i) a[i] = red[i];
 #pragma unroll 2
-  for (int t = 1; t < W; ++t) {
-    const float4 o = *(const float4*)&red[4 * t];
-    m.x = __builtin_elementwise_maximum(m.x, o.x);
-    m.y = __builtin_elementwise_maximum(m.y, o.y);
-    m.z = __builtin_elementwise_maximum(m.z, o.z);
-    m.w = __builtin_elementwise_maximum(m.w, o.w);
-  }
-  a[0] = m.x; a[1] = m.y; a[2] = m.z; a[3] = m.w;
+  for (int t = 1; t < W; ++t)
+#pragma unroll
+    for (int i = 0; i < N; ++i) a[i] = __builtin_elementwise_maximum(a[i], red[N * t + i]);
   __syncthreads();
 }
 
@@ -932,15 +969,17 @@ SJD_DEV void wave_find_from_top(const uint32_t* hist, int target, int* bin, int*
   }
 }
 
-template <int BLOCK, int NC, bool TWO>
+// ROWS: bit 0 selects the target row (v, statistics ps), bit 1 its draft row (u,
+// statistics qs).
+template <int BLOCK, int NC, int ROWS, class Sh>
 SJD_DEV bool fast_select(const float4 (&v)[NC], const float4 (&u)[NC], int V, int top_k, float T,
-                         VSh<BLOCK, NC>& sh, RowStats& ps, RowStats& qs, float lp0, float lq0, float& ep0,
-                         float& eq0) {
-  using Sh = VSh<BLOCK, NC>;
+                         Sh& sh, RowStats& ps, RowStats& qs) {
   constexpr int W = BLOCK / kWave;
   constexpr int CAPW = Sh::CAPW;
-  constexpr int R = TWO ? 2 : 1;
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
+  constexpr bool TGT = (ROWS & 1) != 0, DRF = (ROWS & 2) != 0, TWO = TGT && DRF;
+  constexpr int R0 = TGT ? 0 : 1, R1 = DRF ? 2 : 1;  // rows r in [R0, R1)
+  // (the wave index in a scalar: the append's addresses then need no vector adds)
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), w = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int nchunk = V >> 2;
   const int k = (top_k <= 0 || top_k >= V) ? V : top_k;
   if (k >= V) return false;
@@ -950,18 +989,22 @@ SJD_DEV bool fast_select(const float4 (&v)[NC], const float4 (&u)[NC], int V, in
   float st[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
 #pragma unroll
   for (int i = 0; i < NC; ++i) {
-    st[0] = vmax(st[0], vmax(vmax(v[i].x, v[i].y), vmax(v[i].z, v[i].w)));
-    if (TWO) st[2] = vmax(st[2], vmax(vmax(u[i].x, u[i].y), vmax(u[i].z, u[i].w)));
-    if ((i & 1) == 0 && tid + i * BLOCK < nchunk) {
-      st[1] = vmax(st[1], -v[i].x);
-      if (TWO) st[3] = vmax(st[3], -u[i].x);
+    if (i >= kFullSlots<BLOCK, NC> && i * BLOCK >= nchunk) continue;  // (uniform, as below: slots past the row cost nothing)
+    if constexpr (TGT) st[0] = vmax(st[0], vmax(vmax(v[i].x, v[i].y), vmax(v[i].z, v[i].w)));
+    if constexpr (DRF) st[2] = vmax(st[2], vmax(vmax(u[i].x, u[i].y), vmax(u[i].z, u[i].w)));
+    if ((i & 1) == 0 && (i < kFullSlots<BLOCK, NC> || (i + 1) * BLOCK <= nchunk || tid + i * BLOCK < nchunk)) {
+      if constexpr (TGT) st[1] = vmax(st[1], -v[i].x);
+      if constexpr (DRF) st[3] = vmax(st[3], -u[i].x);
     }
   }
-  block_max4<W>(st, sh.red_f);
-  // the first candidate's weights under both rows' maxima, computed here so
-  // that the accept test after the selection only scales them
-  ep0 = expf(over_T(lp0 - st[0], T));
-  if (TWO) eq0 = expf(over_T(lq0 - st[2], T));
+  if constexpr (TWO) {
+    block_max_n<W, 4>(st, sh.red_f);
+  } else {
+    float s2[2] = {st[2 * R0], st[2 * R0 + 1]};
+    block_max_n<W, 2>(s2, sh.red_f);
+    st[2 * R0] = s2[0];
+    st[2 * R0 + 1] = s2[1];
+  }
   // samples per row
   int S = 0;
 #pragma unroll
@@ -978,7 +1021,7 @@ SJD_DEV bool fast_select(const float4 (&v)[NC], const float4 (&u)[NC], int V, in
   if (rstar > S) return false;
   float sscale[2], soff[2], smn[2], srng[2];
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
+  for (int r = R0; r < R1; ++r) {
     const float mx = st[2 * r];
     smn[r] = -st[2 * r + 1];
     // finite range (a -inf, +inf or NaN sample or maximum sends the row to
@@ -992,24 +1035,24 @@ SJD_DEV bool fast_select(const float4 (&v)[NC], const float4 (&u)[NC], int V, in
 
   // 2. sample histograms; lo = one bin below the bin that holds sample rstar
   //    from the top
-  for (int b = tid; b < R * kFastBins; b += BLOCK) (&sh.f.hist[0][0])[b] = 0;
+  for (int b = tid; b < (R1 - R0) * kFastBins; b += BLOCK) (&sh.hx.hist[R0][0])[b] = 0;
   __syncthreads();
   auto sbin = [&](float l, int r) -> int {
     return (int)__builtin_amdgcn_fmed3f(__builtin_fmaf(l, sscale[r], soff[r]), 0.0f, (float)(kSampBins - 1));
   };
 #pragma unroll
   for (int i = 0; i < NC; i += 2) {
-    if (tid + i * BLOCK < nchunk) {
-      atomicAdd(&sh.f.hist[0][sbin(v[i].x, 0)], 1u);
-      if (TWO) atomicAdd(&sh.f.hist[1][sbin(u[i].x, 1)], 1u);
+    if (i < kFullSlots<BLOCK, NC> || (i + 1) * BLOCK <= nchunk || tid + i * BLOCK < nchunk) {
+      if constexpr (TGT) atomicAdd(&sh.hx.hist[0][sbin(v[i].x, 0)], 1u);
+      if constexpr (DRF) atomicAdd(&sh.hx.hist[1][sbin(u[i].x, 1)], 1u);
     }
   }
   __syncthreads();
-  if (w < R) wave_find_from_top<kSampBins>(sh.f.hist[w], rstar, &sh.bin[w], &sh.above[w]);
+  if (w < R1 - R0) wave_find_from_top<kSampBins>(sh.hx.hist[R0 + w], rstar, &sh.bin[R0 + w], &sh.above[R0 + w]);
   __syncthreads();
   float lo[2];
 #pragma unroll
-  for (int r = 0; r < R; ++r) lo[r] = smn[r] + ((float)sh.bin[r] - 1.0f) * srng[r] * (1.0f / kSampBins);
+  for (int r = R0; r < R1; ++r) lo[r] = smn[r] + ((float)sh.bin[r] - 1.0f) * srng[r] * (1.0f / kSampBins);
 
   // 3. candidates: every entry >= lo, appended to the wave's region
   //    [w * CAPW, w * CAPW + count); a region that would overflow stops
@@ -1018,35 +1061,40 @@ SJD_DEV bool fast_select(const float4 (&v)[NC], const float4 (&u)[NC], int V, in
   bool ovf[2] = {false, false};
 #pragma unroll
   for (int i = 0; i < NC; ++i) {
+    if (i >= kFullSlots<BLOCK, NC> && i * BLOCK >= nchunk) continue;
     const int xb = 4 * (tid + i * BLOCK);  // padding chunks hold -inf and are never taken
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
+    for (int r = R0; r < R1; ++r) {
       const float4 x4 = r == 0 ? v[i] : u[i];
       const bool s0 = x4.x >= lo[r], s1 = x4.y >= lo[r], s2 = x4.z >= lo[r], s3 = x4.w >= lo[r];
       const uint64_t m0 = __ballot(s0), m1 = __ballot(s1), m2 = __ballot(s2), m3 = __ballot(s3);
       const int t0 = __popcll(m0), t1 = __popcll(m1), t2 = __popcll(m2), t3 = __popcll(m3);
       const int tot = t0 + t1 + t2 + t3;
       if (cnt[r] + tot <= CAPW) {
-        int base = w * CAPW + cnt[r];
+        int base = 4 * (w * CAPW + cnt[r]);  // bytes
         auto put = [&](bool s, uint64_t m, float l, int e) {
           if (s) {
-            const int p = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
-                                                         __builtin_amdgcn_mbcnt_lo((uint32_t)m, (uint32_t)base));
-            if (r == 0) {
-              sh.f.cv[p] = l;
-              sh.f.cx[p] = xb + e;
-              if (TWO) sh.f.cq[p] = comp(u[i], e);
-            } else {
-              sh.u.dv[p] = l;
+            const int c = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+            const int p = (c << 2) + base;
+            auto at = [&](auto* arr) { return (decltype(arr))((char*)arr + p); };
+            if constexpr (TGT) {
+              if (r == 0) {
+                *at(&sh.f.cv[0]) = l;
+                *at(&sh.f.cx[0]) = xb + e;
+                if constexpr (TWO) *at(&sh.f.cq[0]) = comp(u[i], e);
+              }
+            }
+            if constexpr (DRF) {
+              if (r == 1) *at(&sh.u.dv[0]) = l;
             }
           }
         };
         put(s0, m0, x4.x, 0);
-        base += t0;
+        base += 4 * t0;
         put(s1, m1, x4.y, 1);
-        base += t1;
+        base += 4 * t1;
         put(s2, m2, x4.z, 2);
-        base += t2;
+        base += 4 * t2;
         put(s3, m3, x4.w, 3);
       } else {
         ovf[r] = true;
@@ -1055,14 +1103,14 @@ SJD_DEV bool fast_select(const float4 (&v)[NC], const float4 (&u)[NC], int V, in
     }
   }
   if (lane == 0) {
-    sh.wcnt[0][w] = ovf[0] ? -1 : cnt[0];
-    if (TWO) sh.wcnt[1][w] = ovf[1] ? -1 : cnt[1];
+    if constexpr (TGT) sh.wcnt[0][w] = ovf[0] ? -1 : cnt[0];
+    if constexpr (DRF) sh.wcnt[1][w] = ovf[1] ? -1 : cnt[1];
   }
   __syncthreads();
   int tot[2] = {0, 0};
   bool bad = false;
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
+  for (int r = R0; r < R1; ++r) {
 #pragma unroll
     for (int t = 0; t < W; ++t) {
       const int c = sh.wcnt[r][t];
@@ -1079,7 +1127,7 @@ SJD_DEV bool fast_select(const float4 (&v)[NC], const float4 (&u)[NC], int V, in
   // 4. histogram of the candidates over [lo, max]
   float scale[2], off[2];
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
+  for (int r = R0; r < R1; ++r) {
     const float mx = st[2 * r];
     scale[r] = (float)kFastBins * __builtin_amdgcn_rcpf(mx - lo[r]);
     if (!(scale[r] < INFINITY) || !(scale[r] > 0.0f)) bad = true;
@@ -1092,10 +1140,10 @@ SJD_DEV bool fast_select(const float4 (&v)[NC], const float4 (&u)[NC], int V, in
   auto fbin = [&](float l, int r) -> int {
     return (int)__builtin_amdgcn_fmed3f(__builtin_fmaf(l, scale[r], off[r]), 0.0f, (float)(kFastBins - 1));
   };
-  for (int b = tid; b < R * kFastBins; b += BLOCK) (&sh.f.hist[0][0])[b] = 0;
-  for (int b = tid; b < R * (kCandCap + 8); b += BLOCK) {
-    (&sh.f.tb_v[0][0])[b] = -INFINITY;
-    (&sh.f.tb_x[0][0])[b] = 0x7FFFFFFF;
+  for (int b = tid; b < (R1 - R0) * kFastBins; b += BLOCK) (&sh.hx.hist[R0][0])[b] = 0;
+  for (int b = tid; b < (R1 - R0) * (kCandCap + 8); b += BLOCK) {
+    (&sh.f.tb_v[R0][0])[b] = -INFINITY;
+    (&sh.f.tb_x[R0][0])[b] = 0x7FFFFFFF;
   }
   if (tid == 0) {
     sh.ncand[0] = 0;
@@ -1103,18 +1151,19 @@ SJD_DEV bool fast_select(const float4 (&v)[NC], const float4 (&u)[NC], int V, in
     sh.fflag = 0;
   }
   __syncthreads();
-  for (int i = lane; i < cnt[0]; i += kWave) atomicAdd(&sh.f.hist[0][fbin(sh.f.cv[w * CAPW + i], 0)], 1u);
-  if (TWO)
-    for (int i = lane; i < cnt[1]; i += kWave) atomicAdd(&sh.f.hist[1][fbin(sh.u.dv[w * CAPW + i], 1)], 1u);
+  if constexpr (TGT)
+    for (int i = lane; i < cnt[0]; i += kWave) atomicAdd(&sh.hx.hist[0][fbin(sh.f.cv[w * CAPW + i], 0)], 1u);
+  if constexpr (DRF)
+    for (int i = lane; i < cnt[1]; i += kWave) atomicAdd(&sh.hx.hist[1][fbin(sh.u.dv[w * CAPW + i], 1)], 1u);
   __syncthreads();
-  if (w < R) wave_find_from_top<kFastBins>(sh.f.hist[w], k, &sh.bin[w], &sh.above[w]);
+  if (w < R1 - R0) wave_find_from_top<kFastBins>(sh.hx.hist[R0 + w], k, &sh.bin[R0 + w], &sh.above[R0 + w]);
   __syncthreads();
   int bs[2], rem[2], cb[2];
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
+  for (int r = R0; r < R1; ++r) {
     bs[r] = sh.bin[r];
     rem[r] = k - sh.above[r];
-    cb[r] = (int)sh.f.hist[r][bs[r]];
+    cb[r] = (int)sh.hx.hist[r][bs[r]];
     bad |= cb[r] > kCandCap;
   }
   if (bad) {
@@ -1130,23 +1179,25 @@ SJD_DEV bool fast_select(const float4 (&v)[NC], const float4 (&u)[NC], int V, in
   double zp = 0.0, zq = 0.0;
   with_unit_T(T, [&](auto ut) {
     constexpr bool UT = decltype(ut)::value;
-    for (int i = lane; i < cnt[0]; i += kWave) {
-      const int s = w * CAPW + i;
-      const float l = sh.f.cv[s];
-      const int bn = fbin(l, 0);
-      float e = -1.0f;
-      if (bn > bs[0]) {
-        e = expf(div_T<UT>(l - mp, T));
-        zp += (double)e;
-      } else if (bn == bs[0]) {
-        const int p = atomicAdd(&sh.ncand[0], 1);
-        sh.f.tb_v[0][p] = l;
-        sh.f.tb_x[0][p] = sh.f.cx[s];
-        sh.f.tb_s[0][p] = s;
+    if constexpr (TGT) {
+      for (int i = lane; i < cnt[0]; i += kWave) {
+        const int s = w * CAPW + i;
+        const float l = sh.f.cv[s];
+        const int bn = fbin(l, 0);
+        float e = -1.0f;
+        if (bn > bs[0]) {
+          e = expf(div_T<UT>(l - mp, T));
+          zp += (double)e;
+        } else if (bn == bs[0]) {
+          const int p = atomicAdd(&sh.ncand[0], 1);
+          sh.f.tb_v[0][p] = l;
+          sh.f.tb_x[0][p] = sh.f.cx[s];
+          sh.f.tb_s[0][p] = s;
+        }
+        sh.f.cv[s] = e;
       }
-      sh.f.cv[s] = e;
     }
-    if (TWO) {
+    if constexpr (DRF) {
       for (int i = lane; i < cnt[1]; i += kWave) {
         const int s = w * CAPW + i;
         const float l = sh.u.dv[s];
@@ -1164,9 +1215,9 @@ SJD_DEV bool fast_select(const float4 (&v)[NC], const float4 (&u)[NC], int V, in
   __syncthreads();
   // 6. exact rank inside each threshold bin: the first rem join the kept set
   //    (and the normaliser), entry rem - 1 is the threshold
-  const int c0 = cb[0], c1 = TWO ? cb[1] : 0;
+  const int c0 = TGT ? cb[0] : 0, c1 = DRF ? cb[1] : 0;
   for (int t = tid; t < c0 + c1; t += BLOCK) {
-    const int r = t < c0 ? 0 : 1;
+    const int r = TGT && t < c0 ? 0 : R1 - 1;
     const int i = t - (r ? c0 : 0);
     const int c = r ? c1 : c0;
     const float vi = sh.f.tb_v[r][i];
@@ -1184,8 +1235,10 @@ SJD_DEV bool fast_select(const float4 (&v)[NC], const float4 (&u)[NC], int V, in
     const bool keep = rank < rem[r];
     const float e = keep ? expf(over_T(vi - (r ? mq : mp), T)) : -1.0f;
     if (r == 0) {
-      sh.f.cv[sh.f.tb_s[0][i]] = e;
-      if (keep) zp += (double)e;
+      if constexpr (TGT) {
+        sh.f.cv[sh.f.tb_s[0][i]] = e;
+        if (keep) zp += (double)e;
+      }
     } else if (keep) {
       zq += (double)e;
     }
@@ -1196,49 +1249,89 @@ SJD_DEV bool fast_select(const float4 (&v)[NC], const float4 (&u)[NC], int V, in
       if (r == 1 && later_tie > 0) sh.fflag = 1;
     }
   }
-  block_sum_d2<W>(zp, zq, sh.red_d);  // (its barriers publish tau and fflag)
+  // the waves' shares of the normalisers (fast_norm adds them); this barrier
+  // publishes tau and fflag too
+  if constexpr (TGT) zp = wave_sum_d_dpp(zp);
+  if constexpr (DRF) zq = wave_sum_d_dpp(zq);
+  if (lane == 0) {
+    if constexpr (TGT) sh.red_d[w] = zp;
+    if constexpr (DRF) sh.red_d[W + w] = zq;
+  }
+  __syncthreads();
   if (sh.fflag) {
     __syncthreads();
     return false;
   }
-  ps.m = mp;
-  ps.T = T;
-  ps.all = false;
-  ps.tau_v = sh.tau_v[0];
-  ps.tau_x = sh.tau_x[0];
-  ps.invZ = 1.0 / zp;
-  if (TWO) {
+  if constexpr (TGT) {
+    ps.m = mp;
+    ps.T = T;
+    ps.all = false;
+    ps.tau_v = sh.tau_v[0];
+    ps.tau_x = sh.tau_x[0];
+  }
+  if constexpr (DRF) {
     qs.m = mq;
     qs.T = T;
     qs.all = false;
     qs.tau_v = sh.tau_v[1];
     qs.tau_x = sh.tau_x[1];
-    qs.invZ = 1.0 / zq;
   }
   return true;
+}
+
+// The normalisers of a row (pair) that fast_select decided, from its waves'
+// shares in LDS: by whichever waves go on to need them.
+template <int W, int ROWS, class Sh>
+SJD_DEV void fast_norm(const Sh& sh, RowStats& ps, RowStats& qs) {
+  double zp = 0.0, zq = 0.0;
+#pragma unroll
+  for (int i = 0; i < W; ++i) {
+    if constexpr (ROWS & 1) zp += sh.red_d[i];
+    if constexpr (ROWS & 2) zq += sh.red_d[W + i];
+  }
+  if constexpr (ROWS & 1) ps.invZ = 1.0 / zp;
+  if constexpr (ROWS & 2) qs.invZ = 1.0 / zq;
 }
 
 // Compact list (index order) of the kept target candidates: bitmap of the
 // kept set, per-word prefix popcounts, then each kept token at its rank with
 // its probability and, if want_q, its draft probability (from the draft
 // logits stored beside it, or read from draft_row).
-template <int BLOCK, int NC>
-SJD_DEV void fast_build_list(VSh<BLOCK, NC>& sh, const RowStats& ps, const RowStats& qs, bool want_q, bool two,
+template <int BLOCK, int NC, class Sh>
+SJD_DEV void fast_build_list(Sh& sh, const RowStats& ps, const RowStats& qs, bool want_q, bool two,
                              const float* draft_row) {
-  using Sh = VSh<BLOCK, NC>;
   constexpr int W = BLOCK / kWave;
   constexpr int NW = Sh::NW;
   constexpr int CAPW = Sh::CAPW;
   const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
-  const int cnt = sh.wcnt[0][w];
+  const int cnt = __builtin_amdgcn_readfirstlane(sh.wcnt[0][w]);
+  // this lane's candidates, and the draft logits at them: read first, so that
+  // their loads are in flight together and through the bitmap's passes (the
+  // first kWave * PL of the wave's; what lies past them is read where it is used)
+  constexpr int PL = CAPW / kWave < 6 ? CAPW / kWave : 6;
+  float es[PL], lq[PL];
+  int xs[PL];
+#pragma unroll
+  for (int t = 0; t < PL; ++t) {
+    es[t] = -1.0f;
+    xs[t] = 0;
+    lq[t] = 0.0f;
+    if (t * kWave >= cnt) continue;  // (uniform over the wave)
+    const int i = lane + t * kWave, s = w * CAPW + i;
+    if (i < cnt) {
+      es[t] = sh.f.cv[s];
+      xs[t] = sh.f.cx[s];
+      if (want_q && es[t] >= 0.0f) lq[t] = two ? sh.f.cq[two ? s : 0] : draft_row[xs[t]];
+    }
+  }
   for (int i = tid; i < NW; i += BLOCK) sh.bm[i] = 0;
   __syncthreads();
-  for (int i = lane; i < cnt; i += kWave) {
-    const int s = w * CAPW + i;
-    if (sh.f.cv[s] >= 0.0f) {
-      const int x = sh.f.cx[s];
-      atomicOr(&sh.bm[x >> 5], 1u << (x & 31));
-    }
+#pragma unroll
+  for (int t = 0; t < PL; ++t)
+    if (es[t] >= 0.0f) atomicOr(&sh.bm[xs[t] >> 5], 1u << (xs[t] & 31));
+  for (int i = lane + PL * kWave; i < cnt; i += kWave) {
+    const int s = w * CAPW + i, x = sh.f.cx[s];
+    if (sh.f.cv[s] >= 0.0f) atomicOr(&sh.bm[x >> 5], 1u << (x & 31));
   }
   __syncthreads();
   constexpr int WPT = NW / BLOCK > 0 ? NW / BLOCK : 1;
@@ -1260,19 +1353,20 @@ SJD_DEV void fast_build_list(VSh<BLOCK, NC>& sh, const RowStats& ps, const RowSt
   __syncthreads();
   with_unit_T(qs.T, [&](auto ut) {
     constexpr bool UT = decltype(ut)::value;
-    for (int i = lane; i < cnt; i += kWave) {
-      const int s = w * CAPW + i;
+    auto put = [&](float e, int x, float l) {
+      const int r = sh.pre[x >> 5] + __popc(sh.bm[x >> 5] & ((1u << (x & 31)) - 1u));
+      sh.hx.x[r] = (uint16_t)x;
+      sh.u.sp.p[r] = (float)((double)e * ps.invZ);
+      if (want_q)
+        sh.u.sp.q[r] = qs.in_set(l, x) ? (float)((double)expf(div_T<UT>(l - qs.m, qs.T)) * qs.invZ) : 0.0f;
+    };
+#pragma unroll
+    for (int t = 0; t < PL; ++t)
+      if (es[t] >= 0.0f) put(es[t], xs[t], lq[t]);
+    for (int i = lane + PL * kWave; i < cnt; i += kWave) {
+      const int s = w * CAPW + i, x = sh.f.cx[s];
       const float e = sh.f.cv[s];
-      if (e >= 0.0f) {
-        const int x = sh.f.cx[s];
-        const int r = sh.pre[x >> 5] + __popc(sh.bm[x >> 5] & ((1u << (x & 31)) - 1u));
-        sh.u.sp.x[r] = (uint16_t)x;
-        sh.u.sp.p[r] = (float)((double)e * ps.invZ);
-        if (want_q) {
-          const float l = two ? sh.f.cq[s] : draft_row[x];
-          sh.u.sp.q[r] = qs.in_set(l, x) ? (float)((double)expf(div_T<UT>(l - qs.m, qs.T)) * qs.invZ) : 0.0f;
-        }
-      }
+      if (e >= 0.0f) put(e, x, !want_q ? 0.0f : two ? sh.f.cq[two ? s : 0] : draft_row[x]);
     }
   });
   __syncthreads();
@@ -1280,8 +1374,8 @@ SJD_DEV void fast_build_list(VSh<BLOCK, NC>& sh, const RowStats& ps, const RowSt
 
 // Softmax weights over a compact list of logits: w[i] = expf((w[i] - m) / T)
 // in place; returns 1 / sum (fp64, fixed order).
-template <int BLOCK, int NC>
-SJD_DEV double softmax_weights(float* w, int n, float m, float T, VSh<BLOCK, NC>& sh) {
+template <int BLOCK, int NC, class Sh>
+SJD_DEV double softmax_weights(float* w, int n, float m, float T, Sh& sh) {
   constexpr int W = BLOCK / kWave;
   double z = 0.0;
   for (int i = threadIdx.x; i < n; i += BLOCK) {
@@ -1292,10 +1386,10 @@ SJD_DEV double softmax_weights(float* w, int n, float m, float T, VSh<BLOCK, NC>
   return 1.0 / block_sum_d<W>(z, sh.red_d);
 }
 
-template <int BLOCK, int NC>
-SJD_DEV bool kept(const VSh<BLOCK, NC>& sh, int x) { return (sh.bm[x >> 5] >> (x & 31)) & 1u; }
-template <int BLOCK, int NC>
-SJD_DEV int rank_of(const VSh<BLOCK, NC>& sh, int x) {
+template <int BLOCK, int NC, class Sh>
+SJD_DEV bool kept(const Sh& sh, int x) { return (sh.bm[x >> 5] >> (x & 31)) & 1u; }
+template <int BLOCK, int NC, class Sh>
+SJD_DEV int rank_of(const Sh& sh, int x) {
   return sh.pre[x >> 5] + __popc(sh.bm[x >> 5] & ((1u << (x & 31)) - 1u));
 }
 
@@ -1308,8 +1402,12 @@ struct Stages {
   // have fixed trip counts so every array index is a compile-time constant.
   SJD_DEV float rho(float py, float qy, int y) const {
     float r = py;
+    if (n > 0) {  // stage 0: its normaliser and draft mass are 1, so p^(1) and q^(1) are p and q exactly
+      const float d = r - qy;
+      r = d > 0.0f ? d : 0.0f;
+    }
 #pragma unroll
-    for (int s = 0; s < 8; ++s) {
+    for (int s = 1; s < 8; ++s) {
       if (s < n) {
         bool ex = false;
 #pragma unroll
@@ -1326,8 +1424,8 @@ struct Stages {
 
 // Race over the compact list: argmin over kept entries with weight w(e) > 0
 // of Exp(1) / w, the exponential of entry e being stream element e.
-template <int BLOCK, int NC, class Wfn>
-SJD_DEV int race_compact(const VSh<BLOCK, NC>& shc, VSh<BLOCK, NC>& sh, int nk, const Stream& rs, Wfn wfn) {
+template <int BLOCK, int NC, class Sh, class Wfn>
+SJD_DEV int race_compact(const Sh& shc, Sh& sh, int nk, const Stream& rs, Wfn wfn) {
   constexpr int W = BLOCK / kWave;
   uint64_t best = kNoKey;
   for (int j = threadIdx.x; 4 * j < nk; j += BLOCK) {
@@ -1338,7 +1436,7 @@ SJD_DEV int race_compact(const VSh<BLOCK, NC>& shc, VSh<BLOCK, NC>& sh, int nk, 
       if (ent < nk) {
         const float w = wfn(ent);
         if (w > 0.0f) {
-          const uint64_t pk = pack_key(exp1(compu(wd, e)) / w, (int)shc.u.sp.x[ent]);
+          const uint64_t pk = pack_key(exp1(compu(wd, e)) / w, (int)shc.hx.x[ent]);
           best = pk < best ? pk : best;
         }
       }
@@ -1374,7 +1472,7 @@ SJD_DEV void draft_candidates(const VerifyArgs& a, Sh& sh, int nk, int excl, int
       for (int e = 0; e < 4; ++e) {
         const int ent = 4 * jj + e;
         if (ent < nk) {
-          const int x = (int)sh.u.sp.x[ent];
+          const int x = (int)sh.hx.x[ent];
           const float pw = sh.u.sp.p[ent];
           if (pw > 0.0f && x != excl) key[4 * q + e] = pack_key(exp1(compu(wd, e)) / pw, x);
         }
@@ -1444,6 +1542,14 @@ SJD_DEV RowStats get_stats(const int32_t* rec, float T) {
   return st;
 }
 
+// The statistics entry of a target row, for the next step's draft rows
+SJD_DEV RowStatsCache row_cache(const VerifyArgs& a, const RowStats& ps) {
+  RowStatsCache c;
+  c.m = ps.m; c.T = ps.T; c.tau_v = ps.tau_v; c.tau_x = ps.tau_x; c.all = ps.all ? 1 : 0;
+  c.top_k = a.top_k; c.tag = a.stats_tag; c.pad = 0; c.invZ = ps.invZ;
+  return c;
+}
+
 // ------------------------------------------------------------ row kernel
 // What a row needs from memory (uniform over the workgroup).
 struct RowLoad {
@@ -1452,12 +1558,12 @@ struct RowLoad {
   bool need_q;  // its draft row is read (a spine row with a valid draft token)
   const float* cur;
   const float* draft;
-  const RowStatsCache* q_cached;  // the draft row's statistics from the previous step, or NULL
+  bool q_known;  // the draft row's statistics are known (qs; its T is the call's):
+  RowStats qs;   //   the previous step's, or k_draft_stats's
 };
 
 // the logits row of (trial, window row)
-SJD_DEV const float* row_logits(const VerifyArgs& a, int row) {
-  const int b = row / a.L, j = row % a.L;
+SJD_DEV const float* row_logits(const VerifyArgs& a, int b, int j) {
   return a.cur + (size_t)b * (a.cur_bstride ? (size_t)a.cur_bstride : (size_t)a.L * a.V) + (size_t)j * a.V;
 }
 
@@ -1465,9 +1571,8 @@ SJD_DEV bool forced_pos(const VerifyArgs& a, long g) {
   return a.row_len > 0 && g >= 0 && (g % (a.row_len + 1)) == a.row_len;
 }
 
-SJD_DEV RowLoad plan_load(const VerifyArgs& a, int row) {
+SJD_DEV RowLoad plan_load(const VerifyArgs& a, int b, int j) {
   RowLoad r;
-  const int b = row / a.L, j = row % a.L;
   const int Km1 = a.K - 1;
   // every word the plan may need that lies in bounds whatever the window
   // says, loaded before any of them is used
@@ -1480,9 +1585,10 @@ SJD_DEV RowLoad plan_load(const VerifyArgs& a, int row) {
   r.valid = !(D_in < 0 || D_in > a.D || a.K * D_in > a.L || n_q < 0 || n_q > n_s);
   r.need_p = false;
   r.need_q = false;
-  r.cur = row_logits(a, row);
+  r.cur = row_logits(a, b, j);
   r.draft = nullptr;
-  r.q_cached = nullptr;
+  r.q_known = false;
+  r.qs = RowStats{};
   if (!r.valid) return r;
   if (j < n_s) {
     const bool is_forced = forced_pos(a, g0 + j);
@@ -1495,7 +1601,20 @@ SJD_DEV RowLoad plan_load(const VerifyArgs& a, int row) {
         r.draft = a.draft + (size_t)b * a.draft_bstride + (size_t)qrow * a.V;
         if (a.stats_in) {
           const RowStatsCache* c = a.stats_in + (size_t)b * a.L + qrow;
-          if (c->tag == a.stats_tag - 1u && c->T == a.T && c->top_k == a.top_k) r.q_cached = c;
+          if (c->tag == a.stats_tag - 1u && c->T == a.T && c->top_k == a.top_k) {
+            r.q_known = true;
+            r.qs.m = c->m; r.qs.tau_v = c->tau_v; r.qs.tau_x = c->tau_x; r.qs.all = c->all != 0; r.qs.invZ = c->invZ;
+          }
+        } else if (a.flags & kFlagDraftStats) {
+          const int32_t* d = a.rec + ((size_t)b * a.L + j) * kRecInts;
+          if (d[6]) {
+            r.q_known = true;
+            r.qs.tau_v = __int_as_float(d[0]);
+            r.qs.tau_x = d[1];
+            r.qs.m = __int_as_float(d[2]);
+            r.qs.invZ = __longlong_as_double((long long)(((uint64_t)(uint32_t)d[4] << 32) | (uint32_t)d[3]));
+            r.qs.all = d[5] != 0;
+          }
         }
       }
     }
@@ -1508,15 +1627,15 @@ SJD_DEV RowLoad plan_load(const VerifyArgs& a, int row) {
   return r;
 }
 
-// One row. With PF, v already holds the row's logits (if ld.need_p) and vq
-// its draft row (if ld.need_q), both loaded at kernel start so that the two
-// reads overlap; without PF, vq is v and each row is loaded when needed.
-template <int BLOCK, int NC, bool PF>
-SJD_DEV void verify_row(const VerifyArgs& a, VSh<BLOCK, NC>& sh, int row, const RowLoad& ld, float4 (&v)[NC],
+// One row, whose logits v holds (if ld.need_p). TWO: vq holds its draft row (if
+// ld.need_q and its statistics are not known), both loaded at kernel start so
+// that the two reads overlap. Otherwise vq is v: the draft row's statistics
+// usually come with ld, and a draft row without them takes v's place.
+template <int BLOCK, int NC, bool TWO>
+SJD_DEV void verify_row(const VerifyArgs& a, VSh<BLOCK, NC, TWO>& sh, int b, int j, const RowLoad& ld, float4 (&v)[NC],
                         float4 (&vq)[NC]) {
   constexpr int W = BLOCK / kWave;
   const int tid = threadIdx.x;
-  const int b = row / a.L, j = row % a.L;
   const int L = a.L, V = a.V, Km1 = a.K - 1;
   const int nchunk = V >> 2;
   if (!ld.valid) return;  // finalize flags the trial
@@ -1528,6 +1647,9 @@ SJD_DEV void verify_row(const VerifyArgs& a, VSh<BLOCK, NC>& sh, int row, const 
   const bool ac = (a.flags & kFlagAC) != 0;
   const bool pd = (a.flags & kFlagPD) != 0 && Km1 > 0;
   const bool spine = j < n_s;
+  const bool inl = pd && (a.flags & kFlagPDInline);
+  // an accepted first draft leaves nothing to draw in this row
+  const bool accept_exits = spine && ac && !inl && !a.dbg_p;
 
   // candidates: the spine draft, then (tree rows) its siblings; an
   // out-of-range or repeated candidate ends the list
@@ -1562,31 +1684,70 @@ SJD_DEV void verify_row(const VerifyArgs& a, VSh<BLOCK, NC>& sh, int row, const 
   // when their stage comes)
   const float qcl0 = ncand > 0 ? ld.draft[stg.cand[0]] : 0.0f;
   const float pcl0 = ncand > 0 ? ld.cur[stg.cand[0]] : 0.0f;
-  // the first accept draw (uniform over the workgroup), ahead of the selection
-  const float u0 = u01(Stream(a.seed, kTagAcc, 0u, (uint32_t)j, (uint32_t)b, a.step).word(0));
-  // candidate path: the first candidate's weights exp((l - max) / T) under
-  // each row's maximum (computed once the maxima are known)
-  float ep0 = 0.0f, eq0 = 0.0f;
 
+  // the first accept draw (uniform over the workgroup): two rows per workgroup,
+  // where latency is what counts, ahead of the selection
+  const float u0 = TWO ? u01(Stream(a.seed, kTagAcc, 0u, (uint32_t)j, (uint32_t)b, a.step).word(0)) : 0.0f;
   RowStats ps{}, qs{};
   int nk = 0;
   bool q_ready = false;  // the draft distribution at the target's kept entries is in sp_q
   // candidate path: the compact list (and sp_q) is built when a draw needs it
   bool lazy = false;
-  bool fast_first = false;  // ep0 / eq0 hold the first candidate's weights
-  const bool two = ld.need_q && !ld.q_cached;
+  const bool two = TWO && ld.need_q && !ld.q_known;
+  if (ld.need_q && ld.q_known) {
+    qs = ld.qs;
+    qs.T = a.T;
+  }
   if (ld.need_p) {
-    if (!PF) load_row<BLOCK, NC>(v, ld.cur, V);
-    if constexpr (PF) {
-      if (!(a.flags & kFlagFullSelect)) {
-        if (two) lazy = fast_select<BLOCK, NC, true>(v, vq, V, a.top_k, a.T, sh, ps, qs, pcl0, qcl0, ep0, eq0);
-        else lazy = fast_select<BLOCK, NC, false>(v, v, V, a.top_k, a.T, sh, ps, qs, pcl0, qcl0, ep0, eq0);
+    if (!(a.flags & kFlagFullSelect)) {
+      if constexpr (TWO) {
+        if (two) lazy = fast_select<BLOCK, NC, 3>(v, vq, V, a.top_k, a.T, sh, ps, qs);
       }
-      if (lazy) {
-        nk = (a.top_k <= 0 || a.top_k >= V) ? V : a.top_k;
-        q_ready = two;
-        fast_first = true;
-      } else if (two) {
+      if (!two) lazy = fast_select<BLOCK, NC, 1>(v, v, V, a.top_k, a.T, sh, ps, qs);
+    }
+    if (lazy) {
+      nk = (a.top_k <= 0 || a.top_k >= V) ? V : a.top_k;
+      q_ready = two;
+      // (one row per workgroup: launches large enough for issue slots to matter)
+      // most rows accept their draft and are then done: one wave decides that
+      // (normaliser, accept draw and test), the others wait for its word
+      if constexpr (!TWO) {
+        if (accept_exits && ncand > 0 && ld.q_known) {
+          if (tid < kWave) {
+            fast_norm<W, 1>(sh, ps, qs);
+            const float pk = ps.prob(pcl0, stg.cand[0]), qk = qs.prob(qcl0, stg.cand[0]);
+            const float u = u01(Stream(a.seed, kTagAcc, 0u, (uint32_t)j, (uint32_t)b, a.step).word(0));
+            const bool acc = qk > 0.0f ? (u < pk / qk) : (pk > 0.0f);
+            if (tid == 0) {
+              sh.dec = acc ? 1 : 0;
+              if (acc) {
+                rec[0] = stg.cand[0];
+                rec[1] = 1;
+                rec[9] = stg.cand[0];
+                put_stats(rec, ps);
+                if (a.out_rows) {
+                  int32_t* o = a.out_rows + ((size_t)b * L + j) * 2;
+                  o[0] = stg.cand[0] + a.vis_lo;
+                  o[1] = 1;
+                }
+                if (a.stats_out) a.stats_out[(size_t)b * L + j] = row_cache(a, ps);
+              }
+            }
+          }
+          __syncthreads();
+          if (sh.dec) return;
+        }
+      }
+      if constexpr (TWO) {
+        if (two) fast_norm<W, 3>(sh, ps, qs);
+        else fast_norm<W, 1>(sh, ps, qs);
+      } else {
+        fast_norm<W, 1>(sh, ps, qs);
+      }
+      __syncthreads();  // (the sums' memory is used again)
+    }
+    if constexpr (TWO) {
+      if (!lazy && two) {
         // target and draft rows together
         float mx2[2], mn2[2];
         row_maxmin2<BLOCK, NC>(v, vq, sh, mx2, mn2);
@@ -1610,7 +1771,7 @@ SJD_DEV void verify_row(const VerifyArgs& a, VSh<BLOCK, NC>& sh, int row, const 
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                   if ((np >> e) & 1u) {
-                    sh.u.sp.x[rp] = (uint16_t)(4 * c + e);
+                    sh.hx.x[rp] = (uint16_t)(4 * c + e);
                     sh.u.sp.p[rp] = comp(v[i], e);
                     sh.u.sp.q[rp] = comp(vq[i], e);
                     ++rp;
@@ -1636,7 +1797,7 @@ SJD_DEV void verify_row(const VerifyArgs& a, VSh<BLOCK, NC>& sh, int row, const 
           qs.invZ = 1.0 / zq;
           for (int i = tid; i < nk; i += BLOCK) {
             sh.u.sp.p[i] = (float)((double)sh.u.sp.p[i] * ps.invZ);
-            const int x = (int)sh.u.sp.x[i];
+            const int x = (int)sh.hx.x[i];
             const bool in_q = (sh.o.bmq[x >> 5] >> (x & 31)) & 1u;
             sh.u.sp.q[i] = in_q ? (float)((double)expf(over_T(sh.u.sp.q[i] - qs.m, a.T)) * qs.invZ) : 0.0f;
           }
@@ -1650,17 +1811,12 @@ SJD_DEV void verify_row(const VerifyArgs& a, VSh<BLOCK, NC>& sh, int row, const 
       ps.m = mx;
       ps.T = a.T;
       nk = select_kept<BLOCK, NC>(v, V, a.top_k, mx, mn, sh, sh.bm, sh.pre, ps);
-      compact_row<BLOCK, NC>(v, V, sh.bm, sh.pre, sh.u.sp.x, sh.u.sp.p);
+      compact_row<BLOCK, NC>(v, V, sh.bm, sh.pre, sh.hx.x, sh.u.sp.p);
       __syncthreads();
       ps.invZ = softmax_weights<BLOCK, NC>(sh.u.sp.p, nk, ps.m, a.T, sh);
       for (int i = tid; i < nk; i += BLOCK) sh.u.sp.p[i] = (float)((double)sh.u.sp.p[i] * ps.invZ);
     }
-    if (a.stats_out && tid == 0) {
-      RowStatsCache c;
-      c.m = ps.m; c.T = ps.T; c.tau_v = ps.tau_v; c.tau_x = ps.tau_x; c.all = ps.all ? 1 : 0;
-      c.top_k = a.top_k; c.tag = a.stats_tag; c.pad = 0; c.invZ = ps.invZ;
-      a.stats_out[(size_t)b * L + j] = c;
-    }
+    if (a.stats_out && tid == 0) a.stats_out[(size_t)b * L + j] = row_cache(a, ps);
     if (a.dbg_p) {
       float4* dst = (float4*)(a.dbg_p + ((size_t)b * L + j) * V);
 #pragma unroll
@@ -1746,22 +1902,26 @@ SJD_DEV void verify_row(const VerifyArgs& a, VSh<BLOCK, NC>& sh, int row, const 
     const float* draft_row = ld.draft;
     if (q_ready) {
       // computed together with the target row
-    } else if (ld.q_cached) {
-      // the previous step computed this row's distribution: its statistics,
-      // and the draft logits at the target's kept entries (gathered)
-      const RowStatsCache c = *ld.q_cached;
-      qs.m = c.m; qs.T = c.T; qs.tau_v = c.tau_v; qs.tau_x = c.tau_x; qs.all = c.all != 0; qs.invZ = c.invZ;
+    } else if (ld.q_known) {
+      // the draft row's statistics were computed before (k_draft_stats, or the
+      // previous step); the draft logits at the target's kept entries are
+      // gathered when the list is built
       if (!lazy) {
         for (int i = tid; i < nk; i += BLOCK) {
-          const int x = (int)sh.u.sp.x[i];
+          const int x = (int)sh.hx.x[i];
           const float l = draft_row[x];
           sh.u.sp.q[i] = qs.in_set(l, x) ? (float)((double)expf(over_T(l - qs.m, a.T)) * qs.invZ) : 0.0f;
         }
         __syncthreads();
       }
     } else {
-    // draft row: selection, then its logits at the kept entries
-    if (!PF) load_row<BLOCK, NC>(vq, draft_row, V);
+    // draft row: selection, then its logits at the kept entries (the target's
+    // list first: the selection takes the candidates' memory)
+    if (lazy) {
+      fast_build_list<BLOCK, NC>(sh, ps, qs, false, false, nullptr);
+      lazy = false;
+    }
+    if (!TWO) load_row<BLOCK, NC>(vq, draft_row, V);
     float qmx, qmn;
     row_maxmin<BLOCK, NC>(vq, sh, qmx, qmn);
     qs.m = qmx;
@@ -1791,7 +1951,7 @@ SJD_DEV void verify_row(const VerifyArgs& a, VSh<BLOCK, NC>& sh, int row, const 
     __syncthreads();
     qs.invZ = softmax_weights<BLOCK, NC>(sh.o.qc, nq, qs.m, a.T, sh);
     for (int i = tid; i < nk; i += BLOCK) {
-      const int x = (int)sh.u.sp.x[i];
+      const int x = (int)sh.hx.x[i];
       const bool in_q = (sh.o.bmq[x >> 5] >> (x & 31)) & 1u;
       sh.u.sp.q[i] = in_q ? (float)((double)expf(over_T(sh.u.sp.q[i] - qs.m, a.T)) * qs.invZ) : 0.0f;
     }
@@ -1809,15 +1969,11 @@ SJD_DEV void verify_row(const VerifyArgs& a, VSh<BLOCK, NC>& sh, int row, const 
       const float lp = k == 1 ? pcl0 : ld.cur[x];
       const float den = 1.0f - Qsum;
       // at stage 1 the normaliser and the remaining draft mass are 1, so
-      // p^(1) and q^(1) are p and q exactly; the weights of the first
-      // candidate are those exp((l - max) / T) the selection computed
-      const bool first_fast = k == 1 && fast_first;
-      const float px = first_fast ? (ps.in_set(lp, x) ? (float)((double)ep0 * ps.invZ) : 0.0f) : ps.prob(lp, x);
-      const float qx = (first_fast && two) ? (qs.in_set(lq, x) ? (float)((double)eq0 * qs.invZ) : 0.0f)
-                                           : qs.prob(lq, x);
+      // p^(1) and q^(1) are p and q exactly
+      const float px = ps.prob(lp, x), qx = qs.prob(lq, x);
       const float pk = k == 1 ? px : stg.rho(px, qx, x) / Nf;
       const float qk = k == 1 ? qx : (den > 0.0f ? qx / den : 0.0f);
-      const float u = k == 1 ? u0 : u01(Stream(a.seed, kTagAcc, (uint32_t)(k - 1), (uint32_t)j, (uint32_t)b, a.step).word(0));
+      const float u = TWO && k == 1 ? u0 : u01(Stream(a.seed, kTagAcc, (uint32_t)(k - 1), (uint32_t)j, (uint32_t)b, a.step).word(0));
       const bool acc = qk > 0.0f ? (u < pk / qk) : (pk > 0.0f);
       if (acc) {
         out_tok = x;
@@ -1837,7 +1993,7 @@ SJD_DEV void verify_row(const VerifyArgs& a, VSh<BLOCK, NC>& sh, int row, const 
       if (k == ncand) break;
       double nd = 0.0;
       for (int ent = tid; ent < nk; ent += BLOCK)
-        nd += (double)stg.rho(sh.u.sp.p[ent], sh.u.sp.q[ent], (int)sh.u.sp.x[ent]);
+        nd += (double)stg.rho(sh.u.sp.p[ent], sh.u.sp.q[ent], (int)sh.hx.x[ent]);
       nd = block_sum_d<W>(nd, sh.red_d);
       if (!(nd > 0.0)) {
         stg.n -= 1;  // no residual mass: draw from p^(k) itself
@@ -1853,7 +2009,7 @@ SJD_DEV void verify_row(const VerifyArgs& a, VSh<BLOCK, NC>& sh, int row, const 
       need_list();
       auto draw = [&]() {
         return race_compact<BLOCK, NC>(sh, sh, nk, rs, [&](int ent) -> float {
-          return stg.rho(sh.u.sp.p[ent], qrow_c(ent), (int)sh.u.sp.x[ent]);
+          return stg.rho(sh.u.sp.p[ent], qrow_c(ent), (int)sh.hx.x[ent]);
         });
       };
       out_tok = draw();
@@ -1884,7 +2040,6 @@ SJD_DEV void verify_row(const VerifyArgs& a, VSh<BLOCK, NC>& sh, int row, const 
   // proactive drafting: a small launch (every row resident at once) draws
   // each row's candidates here; otherwise k_verify_pd draws them for the
   // rows the next window drafts at, from the statistics this row leaves
-  const bool inl = pd && (a.flags & kFlagPDInline);
   int pds[7];
   if (inl) {
     need_list();
@@ -1908,26 +2063,55 @@ SJD_DEV void verify_row(const VerifyArgs& a, VSh<BLOCK, NC>& sh, int row, const 
   }
 }
 
-// One workgroup per row (row = trial * L + window row); for 512 threads or
-// more the register budget is capped so that two workgroups share a compute
-// unit.
-template <int BLOCK, int NC, bool PF>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(BLOCK >= 512 ? 4 : 1))) void k_verify_rows(VerifyArgs a) {
-  __shared__ VSh<BLOCK, NC> sh;
-  const int row = blockIdx.x;
+// One workgroup per row, grid (window rows, trials). TWO: both rows in
+// registers, two 512-thread workgroups to a compute unit; otherwise the target
+// row alone.
+template <int BLOCK, int NC, bool TWO>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(BLOCK < 512 ? 1 : TWO || NC > 8 ? 4 : BLOCK > 512 ? 8 : 6)))
+void k_verify_rows(VerifyArgs a) {
+  __shared__ VSh<BLOCK, NC, TWO> sh;
+  const int j = blockIdx.x, b = blockIdx.y;
   float4 v[NC];
-  if constexpr (PF) {
-    // the row's own logits are read before the plan is known (the row lies
-    // in the logits buffer whatever the window says; a row that turns out to
-    // be unused costs one read)
-    load_row<BLOCK, NC>(v, row_logits(a, row), a.V);
-    const RowLoad ld = plan_load(a, row);
+  // the row's own logits are read before the plan is known (the row lies
+  // in the logits buffer whatever the window says; a row that turns out to
+  // be unused costs one read)
+  load_row<BLOCK, NC>(v, row_logits(a, b, j), a.V);
+  const RowLoad ld = plan_load(a, b, j);
+  if constexpr (TWO) {
     float4 vq[NC];
-    if (ld.need_q && !ld.q_cached) load_row<BLOCK, NC>(vq, ld.draft, a.V);
-    verify_row<BLOCK, NC, true>(a, sh, row, ld, v, vq);
+    if (ld.need_q && !ld.q_known) load_row<BLOCK, NC>(vq, ld.draft, a.V);
+    verify_row<BLOCK, NC, true>(a, sh, b, j, ld, v, vq);
   } else {
-    const RowLoad ld = plan_load(a, row);
-    verify_row<BLOCK, NC, false>(a, sh, row, ld, v, v);
+    verify_row<BLOCK, NC, false>(a, sh, b, j, ld, v, v);
+  }
+}
+
+// Statistics of the draft rows ahead of k_verify_rows<., ., false>, into words
+// 0..6 of each row's record (6: they are there; a row that the candidate path
+// cannot decide is left to the row kernel, which selects it whole). One
+// workgroup per row that has a draft distribution.
+template <int BLOCK, int NC>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(BLOCK < 512 ? 1 : NC > 8 ? 4 : 8)))
+void k_draft_stats(VerifyArgs a) {
+  __shared__ DSh<BLOCK, NC> sh;
+  const int j = blockIdx.x, b = blockIdx.y;
+  const RowLoad ld = plan_load(a, b, j);
+  int32_t* d = a.rec + ((size_t)b * a.L + j) * kRecInts;
+  if (!ld.need_q) return;  // the row kernel does not look
+  float4 v[NC];
+  load_row<BLOCK, NC>(v, ld.draft, a.V);
+  RowStats st{}, none{};
+  const bool ok = fast_select<BLOCK, NC, 2>(v, v, a.V, a.top_k, a.T, sh, none, st);
+  if (threadIdx.x == 0) {
+    if (ok) fast_norm<BLOCK / kWave, 2>(sh, none, st);
+    d[0] = __float_as_int(st.tau_v);
+    d[1] = st.tau_x;
+    d[2] = __float_as_int(st.m);
+    const uint64_t z = (uint64_t)__double_as_longlong(st.invZ);
+    d[3] = (int32_t)(uint32_t)z;
+    d[4] = (int32_t)(uint32_t)(z >> 32);
+    d[5] = 0;  // (the candidate path never keeps every entry)
+    d[6] = ok ? 1 : 0;
   }
 }
 
@@ -2050,9 +2234,11 @@ struct PdSh {
   static constexpr int W = BLOCK / kWave;
   static constexpr int NW = BLOCK * NC / 8;  // bitmap words (32 entries each)
   struct List {
-    uint16_t x[kKcap];
     float p[kKcap];
   };
+  union {
+    uint16_t x[kKcap];
+  } hx;
   uint32_t bm[NW];
   int32_t pre[NW];
   union {
@@ -2081,7 +2267,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(BLOCK >= 
   const int excl = (a.flags & kFlagAC) ? rec[0] : rec[9];
   const RowStats st = get_stats(rec, a.T);
   float4 v[NC];
-  load_row<BLOCK, NC>(v, row_logits(a, b * L + jj), a.V);
+  load_row<BLOCK, NC>(v, row_logits(a, b, jj), a.V);
   bitmap_from_tau<BLOCK, NC>(v, a.V, st, sh.bm);
   __syncthreads();
   constexpr int NW = PdSh<BLOCK, NC>::NW;
@@ -2104,7 +2290,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(BLOCK >= 
   if (tid == BLOCK - 1) sh.ncand[0] = run;
   __syncthreads();
   const int nk = sh.ncand[0];
-  compact_row<BLOCK, NC>(v, a.V, sh.bm, sh.pre, sh.u.sp.x, sh.u.sp.p);
+  compact_row<BLOCK, NC>(v, a.V, sh.bm, sh.pre, sh.hx.x, sh.u.sp.p);
   __syncthreads();
   for (int i = tid; i < nk; i += BLOCK) sh.u.sp.p[i] = (float)((double)expf(over_T(sh.u.sp.p[i] - st.m, a.T)) * st.invZ);
   __syncthreads();
@@ -2154,12 +2340,36 @@ hipError_t launch_verify(const VerifyArgs& a0, const FinalizeOut& o, hipStream_t
   VerifyArgs a = a0;
   const bool pd = (a.flags & kFlagPD) && a.K >= 2 && a.D >= 1;
   if (pd && rows <= kPdInlineRows) a.flags |= kFlagPDInline;
-  const dim3 grid((unsigned)rows);
-  if (a.V <= 4096) hipLaunchKernelGGL((k_verify_rows<256, 4, true>), grid, dim3(256), 0, s, a);
-  else if (a.V <= 16384) hipLaunchKernelGGL((k_verify_rows<512, 8, true>), grid, dim3(512), 0, s, a);
-  else if (a.V <= 32768) hipLaunchKernelGGL((k_verify_rows<1024, 8, true>), grid, dim3(1024), 0, s, a);
-  else if (a.V <= 65536) hipLaunchKernelGGL((k_verify_rows<1024, 16, false>), grid, dim3(1024), 0, s, a);
-  else return hipErrorInvalidValue;
+  const dim3 grid((unsigned)a.L, (unsigned)a.B);
+  if (a.V > kVerifyMaxV || a.B > 65535) return hipErrorInvalidValue;
+  // Both rows at once while the rows fit the chip about twice (one launch, one
+  // chain of phases); beyond that, and where two rows do not fit the registers,
+  // the draft rows' statistics in a kernel of their own: with one row per
+  // workgroup more of them share a compute unit (512 threads: four and three
+  // where there were two) and cover each other's phases. Measured, two rows ->
+  // split (us; top-2000, a tree and placeholders in every window): V = 16384, 640
+  // rows 60 -> 68, 1280 91 -> 94, 2048 120 -> 115, 16384 723 -> 620; V = 4096, 640
+  // rows 49 -> 46, 16384 470 -> 373; V = 32768, 640 rows 100 -> 95, 16384 1589 ->
+  // 1169. 131072 rows of 16384 (a chain, every draft from q): 5270 -> 4355.
+  // (With statistics from the previous step, draft rows are not read.)
+  const bool split = a.V > 32768 || rows > two_row_rows(a.V);
+  if (split && !a.stats_in && !(a.flags & kFlagFullSelect)) {
+    a.flags |= kFlagDraftStats;
+    if (a.V <= 4096) hipLaunchKernelGGL((k_draft_stats<256, 4>), grid, dim3(256), 0, s, a);
+    else if (a.V <= 16384) hipLaunchKernelGGL((k_draft_stats<512, 8>), grid, dim3(512), 0, s, a);
+    else if (a.V <= 32768) hipLaunchKernelGGL((k_draft_stats<1024, 8>), grid, dim3(1024), 0, s, a);
+    else hipLaunchKernelGGL((k_draft_stats<1024, 16>), grid, dim3(1024), 0, s, a);
+  }
+  if (split) {
+    if (a.V <= 4096) hipLaunchKernelGGL((k_verify_rows<256, 4, false>), grid, dim3(256), 0, s, a);
+    else if (a.V <= 16384) hipLaunchKernelGGL((k_verify_rows<512, 8, false>), grid, dim3(512), 0, s, a);
+    else if (a.V <= 32768) hipLaunchKernelGGL((k_verify_rows<1024, 8, false>), grid, dim3(1024), 0, s, a);
+    else hipLaunchKernelGGL((k_verify_rows<1024, 16, false>), grid, dim3(1024), 0, s, a);
+  } else {
+    if (a.V <= 4096) hipLaunchKernelGGL((k_verify_rows<256, 4, true>), grid, dim3(256), 0, s, a);
+    else if (a.V <= 16384) hipLaunchKernelGGL((k_verify_rows<512, 8, true>), grid, dim3(512), 0, s, a);
+    else hipLaunchKernelGGL((k_verify_rows<1024, 8, true>), grid, dim3(1024), 0, s, a);
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_verify_finalize, dim3(a.B), dim3(kWave), 0, s, a, o);
