@@ -303,10 +303,10 @@ const RecordedPlan kRecordedPlans[] = {
     // {projection (0 QKV, 1 O, 2 gate|up, 3 down), N, K, row class (0: windows
     //  of <= 32 rows, 1: more), splits, 8 column blocks per workgroup}
     // 7B shape (d 4096, 32 x 128 heads, FFN 11008)
-    {0, 12288, 4096, 0, 5, 1}, {1, 4096, 4096, 0, 8, 0}, {2, 22016, 4096, 0, 2, 1}, {3, 4096, 11008, 0, 8, 0},
+    {0, 12288, 4096, 0, 2, 0}, {1, 4096, 4096, 0, 8, 0}, {2, 22016, 4096, 0, 2, 1}, {3, 4096, 11008, 0, 8, 0},
     {0, 12288, 4096, 1, 5, 1}, {1, 4096, 4096, 1, 8, 0}, {2, 22016, 4096, 1, 2, 1}, {3, 4096, 11008, 1, 15, 1},
     // 8B GQA shape (d 4096, 32 / 8 x 128 heads, FFN 14336); its O projection is the 7B one
-    {0, 6144, 4096, 0, 5, 0}, {2, 28672, 4096, 0, 2, 1}, {3, 4096, 14336, 0, 8, 0},
+    {0, 6144, 4096, 0, 4, 0}, {2, 28672, 4096, 0, 2, 1}, {3, 4096, 14336, 0, 8, 0},
     {0, 6144, 4096, 1, 5, 0}, {2, 28672, 4096, 1, 2, 1}, {3, 4096, 14336, 1, 16, 1},
     // mid shape (d 1024, 16 x 64 heads, FFN 2816)
     {0, 3072, 1024, 0, 8, 0}, {1, 1024, 1024, 0, 8, 0}, {2, 5632, 1024, 0, 5, 0}, {3, 1024, 2816, 0, 22, 0},

@@ -257,6 +257,10 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
   // at one workgroup per compute unit or fewer nothing else hides a
   // workgroup's load latency: keep more weight tiles in flight
   const bool lone = grid.x <= 256;
+  // 8 waves have half of that latency covered among themselves: deeper only where
+  // compute units stay idle (32 rows, gate | up 172 workgroups 34.3 -> 33.0 us; QKV
+  // 240 20.0 -> 21.3, and at 64 rows 23.2 -> 31, LM head 81 -> 108)
+  const bool sparse = grid.x <= 192;
   if (g.fours && !g.wide && MT == 1) {
     hipLaunchKernelGGL((k_gemm<kRingDeep, 1, kGWaves, true>), grid, block, 0, s, g);
   } else if (g.fours && !g.wide) {
@@ -274,7 +278,10 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
     }
   } else if (g.wide) {
     switch (MT) {
-      case 1: hipLaunchKernelGGL((k_gemm<kRingDepth, 1, kGWavesWide>), grid, block, 0, s, g); break;
+      case 1:
+        if (sparse) hipLaunchKernelGGL((k_gemm<kRingDeep, 1, kGWavesWide>), grid, block, 0, s, g);
+        else hipLaunchKernelGGL((k_gemm<kRingDepth, 1, kGWavesWide>), grid, block, 0, s, g);
+        break;
       case 2: hipLaunchKernelGGL((k_gemm<kRingDepth, 2, kGWavesWide>), grid, block, 0, s, g); break;
       case 3: hipLaunchKernelGGL((k_gemm<kRingDepth, 3, kGWavesWide>), grid, block, 0, s, g); break;
       default: hipLaunchKernelGGL((k_gemm<kRingDepth, 4, kGWavesWide>), grid, block, 0, s, g); break;
@@ -285,7 +292,10 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
         if (lone) hipLaunchKernelGGL((k_gemm<kRingDeep, 1, kGWaves>), grid, block, 0, s, g);
         else hipLaunchKernelGGL((k_gemm<kRingDepth, 1, kGWaves>), grid, block, 0, s, g);
         break;
-      case 2: hipLaunchKernelGGL((k_gemm<kRingDepth, 2, kGWaves>), grid, block, 0, s, g); break;
+      case 2:
+        if (lone) hipLaunchKernelGGL((k_gemm<kRingDeep, 2, kGWaves>), grid, block, 0, s, g);
+        else hipLaunchKernelGGL((k_gemm<kRingDepth, 2, kGWaves>), grid, block, 0, s, g);
+        break;
       case 3: hipLaunchKernelGGL((k_gemm<kRingDepth, 3, kGWaves>), grid, block, 0, s, g); break;
       default: hipLaunchKernelGGL((k_gemm<kRingDepth, 4, kGWaves>), grid, block, 0, s, g); break;
     }
