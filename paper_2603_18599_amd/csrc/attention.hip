@@ -1,4 +1,4 @@
-// Window attention: M <= 64 query slots of one head against the cached keys
+// Window attention: the query slots of one head against the cached keys
 // and values plus the window's own (tree-masked) keys, on bf16 MFMA.
 //
 // Layout choices (gfx950, wave64, v_mfma_f32_32x32x16_bf16):
@@ -33,6 +33,20 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 SJD_DEV bf16x8 to_bf16x8(const uint4& u) { return __builtin_bit_cast(bf16x8, u); }
+
+// What 32-slot block z attends to: n cached rows, then Ms window rows. One block
+// of a multi-stream window is one stream. One stream's window is taken in parts
+// of 64 rows (prefill windows hold several; a step's is one): a part's cached rows
+// are the rows before it, and its rows' ancestor masks count from its first row.
+SJD_DEV void part_rows(const AttnArgs& a, int z, int& n, int& Ms) {
+  n = stream_rows(a.st, a.n_dev ? *a.n_dev : a.n_host, z);
+  Ms = a.st.L;
+  if (a.st.mode == kStreamsOne) {
+    const int r0 = z / 2 * 64;
+    n += r0;
+    Ms = a.M - r0 < 64 ? a.M - r0 : 64;
+  }
+}
 
 template <int HD>
 struct AttnSmem {
@@ -175,8 +189,9 @@ __global__ __launch_bounds__(256) void k_attn_partial(AttnArgs a) {
   // positions, L slots each); otherwise the M slots are one stream
   const bool two = a.st.mode != kStreamsOne;
   const int z = blockIdx.z;
-  const int n = stream_rows(a.st, a.n_dev ? *a.n_dev : a.n_host, z);
-  const int Ms = two ? a.st.L : a.M, nk = n + Ms;
+  int n, Ms;
+  part_rows(a, z, n, Ms);
+  const int nk = n + Ms;
   const int kbeg = sp * kAttnChunk;
   if (kbeg >= nk) return;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, r32 = lane & 31, half = lane >> 5;
@@ -184,7 +199,7 @@ __global__ __launch_bounds__(256) void k_attn_partial(AttnArgs a) {
   const int zs = blockIdx.z * 32;  // this workgroup's 32 query slots start here
   const int slot = r32;            // local slot (MFMA column)
   const int gslot = zs + slot;
-  const bool slot_ok = two ? slot < Ms : gslot < Ms;
+  const bool slot_ok = two ? slot < Ms : gslot < a.M;
   const size_t so = two ? (size_t)z * a.sstride : 0;
   const uint16_t* kc = a.kc + so;
   const uint16_t* kc_lo = a.kc_lo + so;
@@ -293,15 +308,16 @@ __global__ __launch_bounds__(256) void k_attn_partial_px(AttnArgs a) {
   const int g0 = part * G;               // the first of them, within the key / value head's group
   const bool two = a.st.mode != kStreamsOne;
   const int z = blockIdx.z;
-  const int n = stream_rows(a.st, a.n_dev ? *a.n_dev : a.n_host, z);
-  const int Ms = two ? a.st.L : a.M, nk = n + Ms;
+  int n, Ms;
+  part_rows(a, z, n, Ms);
+  const int nk = n + Ms;
   const int kbeg = sp * kAttnChunk;
   if (kbeg >= nk) return;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, half = lane >> 5;
   const int zs = blockIdx.z * 32;
   const int slot = lane & 31;
   const int gslot = zs + slot;
-  const bool slot_ok = two ? slot < Ms : gslot < Ms;
+  const bool slot_ok = two ? slot < Ms : gslot < a.M;
   const size_t hbase = (size_t)kvh * a.cap * HD + (two ? (size_t)z * a.sstride : 0);
   const int kb = kbeg + wave * 32;  // this wave's key block
   const bool has = kb < nk;
@@ -493,8 +509,9 @@ __global__ __launch_bounds__(64) void k_attn_combine(AttnArgs a) {
     *(uint4*)(out + kActLo) = make_uint4(0, 0, 0, 0);
     return;
   }
-  const int n = stream_rows(a.st, a.n_dev ? *a.n_dev : a.n_host, slot >> 5);
-  const int nk = n + (two ? a.st.L : a.M);
+  int n, Ms;
+  part_rows(a, slot >> 5, n, Ms);
+  const int nk = n + Ms;
   const int ns = (nk + kAttnChunk - 1) / kAttnChunk;
   const float* wml = a.ws_ml + (size_t)h * a.nsplit_max * kWinRows * 2 + slot * 2;
   const float* wo = a.ws_o + ((size_t)h * a.nsplit_max * kWinRows + slot) * HD + dim0;
@@ -564,12 +581,13 @@ __global__ __launch_bounds__(512) void k_attn_whole(AttnArgs a) {
   __shared__ AttnWholeSmem<HD> sm;
   const int h = blockIdx.x, z = blockIdx.y;
   const bool two = a.st.mode != kStreamsOne;
-  const int n = stream_rows(a.st, a.n_dev ? *a.n_dev : a.n_host, z);
-  const int Ms = two ? a.st.L : a.M, nk = n + Ms;
+  int n, Ms;
+  part_rows(a, z, n, Ms);
+  const int nk = n + Ms;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, slot = lane & 31, half = lane >> 5;
   const int grp = wave >> 2;  // chunk of this wave within an iteration
   const int zs = z * 32, gslot = zs + slot;
-  const bool slot_ok = two ? slot < Ms : gslot < Ms;
+  const bool slot_ok = two ? slot < Ms : gslot < a.M;
   const size_t hb = (size_t)(h / (a.H / a.Hkv)) * a.cap * HD + (two ? (size_t)z * a.sstride : 0);
   if (wave < 2 * NQ) {
     const int p = wave / NQ, t = wave % NQ;
@@ -644,7 +662,7 @@ __global__ __launch_bounds__(512) void k_attn_whole(AttnArgs a) {
 
 hipError_t launch_attention(const AttnArgs& a, int hd, hipStream_t s) {
   if (a.M > 32 * a.mtiles) return hipErrorInvalidValue;
-  if (a.M < 1 || a.M > (a.st.mode == kStreamsOne ? 64 : 32 * kMaxStreams)) return hipErrorInvalidValue;
+  if (a.M < 1 || a.M > kWinRows) return hipErrorInvalidValue;
   const unsigned zh = (unsigned)(a.M + 31) / 32;  // 32-slot blocks
   const dim3 g1(a.H, a.nsplit_max, zh), g2(a.H, hd / 64, (unsigned)(a.M + 7) / 8);
   if (hd == 128) {

@@ -118,7 +118,8 @@ SJD_DEV void window_row(const WindowIn& in, int a, int& tok, int& pos, uint64_t&
   if (!in.st) {  // prefill: a causal chain
     tok = in.prompt[in.start + a];
     pos = in.start + a;
-    anc = a == 63 ? ~0ull : ((1ull << (a + 1)) - 1ull);
+    const int r = a & 63;  // within its 64-row part (see launch_attention)
+    anc = r == 63 ? ~0ull : ((1ull << (r + 1)) - 1ull);
     return;
   }
   const Streams& sm = in.sm;
@@ -202,7 +203,7 @@ __global__ __launch_bounds__(256) void k_window_in(WindowIn a) {
 hipError_t launch_window_in(const WindowIn& a, hipStream_t s) {
   const bool multi = a.sm.mode != kStreamsOne;
   if (a.M < 1 || a.M > kWinRows || a.M > 32 * a.mtiles || a.vis_lo < 0 || a.vis_lo >= a.vocab || (!a.st && !a.prompt) ||
-      (multi && (a.sm.nz < 1 || a.sm.nz > kMaxStreams || a.L > 32)) || (!multi && a.M > 64))
+      (multi && (a.sm.nz < 1 || a.sm.nz > kMaxStreams || a.L > 32)) || (!multi && a.st && a.M > 64))
     return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_window_in, dim3(norm_chunks(a.d), (a.M + 7) / 8), dim3(256), 0, s, a);
   return hipGetLastError();

@@ -29,8 +29,12 @@ struct Ctx {
   sjd_config c{};
   int cap = 0;      // KV rows
   int cap_pad = 0;  // row stride of the caches (multiple of the attention chunk)
-  int Mpad = 64;  // activation rows (window rows: one stream of <= 64, or up to four streams of 32)
-  static constexpr int kPrefillRows = 64;  // prefill windows (one stream)
+  // activation rows: windows of one stream of <= 64 or of up to four streams of
+  // 32; prefill windows of one stream. Prefill streams the weights once per
+  // window, and 128 rows of the GEMM take 1.45 times as long as 64 (7B shape,
+  // prompt 500: 9.8 -> 7.2 ms); its attention masks within 64-row parts.
+  static constexpr int kPrefillRows = 128;
+  int Mpad = kPrefillRows;
   // library-owned weights: embedding and norm gains as bf16 rows, matrices
   // in the GEMM tile layout; lw[l] = {attn_norm, wqkv, -, -, wo, ffn_norm, wgu, -, wd}
   const uint16_t* embed = nullptr;
@@ -186,14 +190,17 @@ int forward(Ctx& x, int M, const int32_t* prompt, const int32_t* n_dev, int n_ho
   const sjd_config& c = x.c;
   const int d = c.d_model, H = c.n_heads, Hkv = c.n_kv_heads, hd = c.head_dim, F = c.ffn_dim;
   const int Nq = H * hd, Nkv = Hkv * hd, Nqkv = Nq + 2 * Nkv;
+  const int mt = (M + 31) / 32;  // row tiles of this window's activations
   sjd::WindowIn in{};
   in.st = prompt ? nullptr : x.st; in.prompt = prompt; in.start = n_host; in.M = M; in.L = c.L; in.K = c.K;
   in.vis_lo = c.vis_lo; in.sm = sm; in.win = x.win; in.E = x.embed; in.d = d; in.vocab = c.vocab_size; in.x = x.x;
-  in.g = x.lw[0][0]; in.y = x.xn; in.mtiles = x.mtiles; in.ss = x.ss; in.fours = x.fours;
+  in.g = x.lw[0][0]; in.y = x.xn; in.mtiles = mt; in.ss = x.ss; in.fours = x.fours;
   HIPTRY(sjd::launch_window_in(in, s));
   const size_t qplane = (size_t)x.Mpad * Nqkv, rplane = (size_t)x.Mpad * d, guplane = (size_t)x.Mpad * 2 * F;
   int pend = 0;  // partial planes of the last residual projection not yet added into x
-  const Ctx::Plan* P = M > 64 ? x.plan_wide : x.plan[M > 32 ? 1 : 0];
+  // (prefill rows take the 64-row plan in windows of any length, so that a row's
+  // summation order does not depend on its window)
+  const Ctx::Plan* P = M > 64 && !prompt ? x.plan_wide : x.plan[M > 32 ? 1 : 0];
   sjd::GemmArgs normed{};  // GEMM arguments that apply the RMSNorm row scale
   normed.ss = x.ss;
   normed.ss_n = sjd::norm_chunks(d);
@@ -209,10 +216,10 @@ int forward(Ctx& x, int M, const int32_t* prompt, const int32_t* n_dev, int n_ho
     a.n_dev = n_dev; a.n_host = n_host; a.M = M; a.H = H; a.Hkv = Hkv; a.cap = x.cap_pad;
     a.scale = (float)(1.4426950408889634 / std::sqrt((double)hd));
     a.ws_o = x.attn_o; a.ws_ml = x.attn_ml; a.nsplit_max = x.nsplit_max; a.out = x.att;
-    a.mtiles = x.mtiles; a.qparts = x.qparts; a.whole = x.fused ? 1 : 0;
+    a.mtiles = mt; a.qparts = x.qparts; a.whole = x.fused ? 1 : 0;
     if (x.fused) {
       sjd::FusedArgs f{};
-      f.mtiles = x.mtiles; f.M = M; f.inv_d = 1.0f / (float)d; f.eps = c.rms_eps;
+      f.mtiles = mt; f.M = M; f.inv_d = 1.0f / (float)d; f.eps = c.rms_eps;
       f.nch = f.nch_out = sjd::norm_chunks(d); f.fours = f.fours_out = x.fours; f.x = x.x;
       f.win = x.win; f.n_dev = n_dev; f.n_host = n_host; f.H = H; f.Hkv = Hkv; f.hd = hd; f.cap = x.cap_pad;
       f.rope = x.rope; f.kv = kv; f.st = sm;
@@ -227,10 +234,10 @@ int forward(Ctx& x, int M, const int32_t* prompt, const int32_t* n_dev, int n_ho
           return SJD_OK;
         }
         sjd::GemmArgs g{};
-        g.A = A; g.mtiles = x.mtiles; g.M = M; g.W = W; g.N = d; g.K = K; g.S = S; g.wide = wide;
+        g.A = A; g.mtiles = mt; g.M = M; g.W = W; g.N = d; g.K = K; g.S = S; g.wide = wide;
         g.out = x.rpart; g.plane = rplane; g.ldo = d;
         HIPTRY(sjd::launch_gemm(g, s));
-        HIPTRY(sjd::launch_resid_norm(x.x, x.rpart, S, rplane, gain, M, d, x.xn, x.mtiles, nullptr, x.fours, s));
+        HIPTRY(sjd::launch_resid_norm(x.x, x.rpart, S, rplane, gain, M, d, x.xn, mt, nullptr, x.fours, s));
         return SJD_OK;
       };
       TRY(resid(x.att, w[4], Nq, P[kProjO].S, P[kProjO].wide, w[5]));
@@ -240,26 +247,26 @@ int forward(Ctx& x, int M, const int32_t* prompt, const int32_t* n_dev, int n_ho
       continue;
     }
     if (l > 0)  // (layer 0's input comes normed from launch_window_in)
-      HIPTRY(sjd::launch_resid_norm(x.x, x.rpart, pend, rplane, w[0], M, d, x.xn, x.mtiles, x.ss, nullptr, s));
+      HIPTRY(sjd::launch_resid_norm(x.x, x.rpart, pend, rplane, w[0], M, d, x.xn, mt, x.ss, nullptr, s));
     sjd::GemmArgs g = normed;
-    g.A = x.xn; g.mtiles = x.mtiles; g.M = M; g.W = w[1]; g.N = Nqkv; g.K = d; g.S = P[kProjQkv].S;
+    g.A = x.xn; g.mtiles = mt; g.M = M; g.W = w[1]; g.N = Nqkv; g.K = d; g.S = P[kProjQkv].S;
     g.wide = P[kProjQkv].wide; g.out = x.qkv; g.plane = qplane; g.ldo = Nqkv;
     HIPTRY(sjd::launch_gemm(g, s));
     HIPTRY(sjd::launch_rope_kv(x.qkv, P[kProjQkv].S, qplane, x.win, n_dev, n_host, M, H, Hkv, hd, x.rope, kv, x.cap_pad,
                                sm, s));
     HIPTRY(sjd::launch_attention(a, hd, s));
     g = sjd::GemmArgs{};
-    g.A = x.att; g.mtiles = x.mtiles; g.M = M; g.W = w[4]; g.N = d; g.K = Nq; g.S = P[kProjO].S;
+    g.A = x.att; g.mtiles = mt; g.M = M; g.W = w[4]; g.N = d; g.K = Nq; g.S = P[kProjO].S;
     g.wide = P[kProjO].wide; g.out = x.rpart; g.plane = rplane; g.ldo = d;
     HIPTRY(sjd::launch_gemm(g, s));
-    HIPTRY(sjd::launch_resid_norm(x.x, x.rpart, P[kProjO].S, rplane, w[5], M, d, x.xn, x.mtiles, x.ss, nullptr, s));
+    HIPTRY(sjd::launch_resid_norm(x.x, x.rpart, P[kProjO].S, rplane, w[5], M, d, x.xn, mt, x.ss, nullptr, s));
     g = normed;
-    g.A = x.xn; g.mtiles = x.mtiles; g.M = M; g.W = w[6]; g.N = 2 * F; g.K = d; g.S = P[kProjGu].S;
+    g.A = x.xn; g.mtiles = mt; g.M = M; g.W = w[6]; g.N = 2 * F; g.K = d; g.S = P[kProjGu].S;
     g.wide = P[kProjGu].wide; g.out = x.gup; g.plane = guplane; g.ldo = 2 * F;
     HIPTRY(sjd::launch_gemm(g, s));
-    HIPTRY(sjd::launch_swiglu(x.gup, P[kProjGu].S, guplane, M, F, x.hbuf, x.mtiles, s));
+    HIPTRY(sjd::launch_swiglu(x.gup, P[kProjGu].S, guplane, M, F, x.hbuf, mt, s));
     g = sjd::GemmArgs{};
-    g.A = x.hbuf; g.mtiles = x.mtiles; g.M = M; g.W = w[8]; g.N = d; g.K = F; g.S = P[kProjDown].S;
+    g.A = x.hbuf; g.mtiles = mt; g.M = M; g.W = w[8]; g.N = d; g.K = F; g.S = P[kProjDown].S;
     g.wide = P[kProjDown].wide; g.out = x.rpart; g.plane = rplane; g.ldo = d;
     HIPTRY(sjd::launch_gemm(g, s));
     pend = P[kProjDown].S;
@@ -270,9 +277,9 @@ int forward(Ctx& x, int M, const int32_t* prompt, const int32_t* n_dev, int n_ho
       g.ss = nullptr;
       g.fours = x.fours;
     } else {
-      HIPTRY(sjd::launch_resid_norm(x.x, x.rpart, pend, rplane, x.fnorm, M, d, x.xn, x.mtiles, x.ss, nullptr, s));
+      HIPTRY(sjd::launch_resid_norm(x.x, x.rpart, pend, rplane, x.fnorm, M, d, x.xn, mt, x.ss, nullptr, s));
     }
-    g.A = x.xn; g.mtiles = x.mtiles; g.M = M; g.W = x.head; g.N = c.V; g.K = d; g.S = 1;
+    g.A = x.xn; g.mtiles = mt; g.M = M; g.W = x.head; g.N = c.V; g.K = d; g.S = 1;
     g.wide = c.V >= kWideHeadV ? 1 : 0;
     g.out = logits; g.plane = 0; g.ldo = c.V;
     if (sm.mode == sjd::kStreamsMulti && sm.guided) {  // rows [32 b, 32 b + L): image b's guided logits
@@ -485,7 +492,6 @@ extern "C" int sjd_init(const sjd_config* cfg, const sjd_weights* w, void* strea
   x.use_graph = !(c.flags & SJD_EAGER);
   x.B = c.batch > 1 ? c.batch : 1;
   x.nstreams = x.B * (x.guided ? 2 : 1);
-  x.Mpad = x.nstreams > 2 ? 32 * x.nstreams : 64;
   x.mtiles = x.Mpad / 32;
   auto fail = [&](int rc) {
     sjd_destroy(h);
@@ -605,7 +611,7 @@ extern "C" int sjd_init(const sjd_config* cfg, const sjd_weights* w, void* strea
   const int Nqkv = Nq + 2 * Nkv;
   // one plan per projection and row class (windows of <= 32 rows; of more:
   // timed only for contexts whose steps run them, else the closed form, which
-  // serves their 64-row prefill windows)
+  // serves their prefill windows)
   const int kind_N[4] = {Nqkv, d, 2 * F, d}, kind_K[4] = {d, Nq, d, F};
   const bool step64 = x.nstreams > 1 || c.L > 32;
   struct Proj { int kind, N, K, cls; Ctx::Plan closed; std::vector<Ctx::Plan> cand; bool tune; };
@@ -753,13 +759,16 @@ extern "C" int sjd_init(const sjd_config* cfg, const sjd_weights* w, void* strea
 
 namespace {
 
-// Caches the first n - 1 prompt tokens (windows of Mpad rows) into the caches
-// of stream `cache`.
+// Caches the first n - 1 prompt tokens (windows of kPrefillRows rows) into the
+// caches of stream `cache`.
 int prefill_stream(Ctx& x, const int32_t* d_prompt, int n, int cache, hipStream_t s) {
   const sjd::Streams one{sjd::kStreamsOne, 0, 0, 0, nullptr};
   const int P = Ctx::kPrefillRows;
-  for (int start = 0; start < n - 1; start += P) {
-    const int M = (n - 1 - start) < P ? (n - 1 - start) : P;
+  for (int start = 0, M; start < n - 1; start += M) {
+    const int rem = n - 1 - start;
+    M = rem < P ? rem : P;
+    // a last part of up to 32 rows is a window of its own: it runs the 32-row plan
+    if (rem > 64 && rem <= 96) M = 64;
     TRY(forward(x, M, d_prompt, nullptr, start, nullptr, one, cache, s));
   }
   return SJD_OK;
