@@ -52,8 +52,9 @@ struct GemmArgs {
   // product row 64 b + m, u = product row 64 b + 32 + m
   int cfg_rows;
   float cfg_w;
-  // 8 column blocks per workgroup (else 4): half the activation loads per
-  // weight byte; the grid is N / 256 column groups x S
+  // 8 column blocks per workgroup (else 4): half the activation loads per weight
+  // byte; the grid is N / 256 column groups x S. (launch_gemm runs it 6 wide where
+  // that fills more compute units; the width does not change a result.)
   int wide;
 };
 

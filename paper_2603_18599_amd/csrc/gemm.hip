@@ -119,11 +119,11 @@ __global__ __launch_bounds__(NW * kWave) void k_gemm(GemmArgs g) {
   // in chunk i of lane r32 + 32*half of row tile mt. The 8 MT staged chunks
   // of a k-step (row tile, plane, chunk) are numbered q = (mt 2 + plane) 4 +
   // chunk, their order in memory, and wave w stages q = w, w + NW, ...
-  constexpr int NS = 8 * MT / NW;  // chunks staged per wave
-  static_assert(NS >= 1 && NS * NW == 8 * MT, "staging split");
+  constexpr int NS = (8 * MT + NW - 1) / NW;  // chunks staged per wave (6 waves: some chunks by two of them)
+  constexpr int NCH = 8 * MT;
   const uint16_t* wp = g.W + (size_t)(active ? nb : 0) * 2048 + (size_t)lane * 8;
   const size_t wstep = (size_t)nblk * 2048;  // next k-step of the same column block
-  const uint16_t* ap = g.A + (size_t)wave * 512 + (size_t)lane * 8;
+  const uint16_t* ap = g.A + (size_t)lane * 8;
   const size_t astep = (size_t)g.mtiles * 4096;
 
   f32x16 acc[MT];
@@ -140,7 +140,7 @@ __global__ __launch_bounds__(NW * kWave) void k_gemm(GemmArgs g) {
   auto issue = [&](int t, int slot) {
     const int st = kstep(t);
 #pragma unroll
-    for (int j = 0; j < NS; ++j) ra[slot][j] = *(const u32x4*)(ap + (size_t)st * astep + j * NW * 512);
+    for (int j = 0; j < NS; ++j) ra[slot][j] = *(const u32x4*)(ap + (size_t)st * astep + (wave + j * NW) % NCH * 512);
     const uint16_t* src = t < n ? wp + (size_t)st * wstep : wpad;
 #pragma unroll
     for (int i = 0; i < 4; ++i) w[slot][i] = __builtin_nontemporal_load((const u32x4*)(src + i * 512));
@@ -148,7 +148,7 @@ __global__ __launch_bounds__(NW * kWave) void k_gemm(GemmArgs g) {
   auto stage = [&](int t, int slot, int buf) {
     const u32x4 z = {0u, 0u, 0u, 0u};
 #pragma unroll
-    for (int j = 0; j < NS; ++j) (&sm.a[buf][0][0][0][0])[(wave + j * NW) * kWave + lane] = t < n ? ra[slot][j] : z;
+    for (int j = 0; j < NS; ++j) (&sm.a[buf][0][0][0][0])[(wave + j * NW) % NCH * kWave + lane] = t < n ? ra[slot][j] : z;
   };
 
   if (n > 0) {
@@ -252,7 +252,14 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
   const int MT = (g.M + 31) / 32;
   if (g.fours && (g.ss || g.ss_n > kFusedMaxChunks)) return hipErrorInvalidValue;
   if (g.cfg_rows < 0 || g.cfg_rows > 32 || (g.cfg_rows > 0 && (MT & 1))) return hipErrorInvalidValue;
-  const int nw = g.wide ? kGWavesWide : kGWaves;
+  // Eight blocks wide, a grid well short of one workgroup per compute unit leaves
+  // the others idle, and one unit does not draw more than about 55 GB/s: six wide
+  // if that still is at most one each (7B gate | up at 2 splits: 172 -> 230
+  // workgroups; with its consumer 36.4 -> 34.2 us at 32 rows, 44.7 -> 43.3 at 64; at 128 rows the step
+  // lost 2%)
+  const auto groups = [&](int w) { return (g.N / 32 + w - 1) / w * g.S; };
+  const bool six = g.wide && !g.fours && MT <= 2 && groups(kGWavesWide) <= 192 && groups(6) > 192 && groups(6) <= 256;
+  const int nw = six ? 6 : g.wide ? kGWavesWide : kGWaves;
   const dim3 grid((unsigned)(((g.N / 32 + nw - 1) / nw) * g.S)), block((unsigned)(nw * kWave));
   // at one workgroup per compute unit or fewer nothing else hides a
   // workgroup's load latency: keep more weight tiles in flight
@@ -276,6 +283,9 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
       case 3: hipLaunchKernelGGL((k_gemm<kRingDepth, 3, kGWavesWide, true>), grid, block, 0, s, g); break;
       default: hipLaunchKernelGGL((k_gemm<kRingDepth, 4, kGWavesWide, true>), grid, block, 0, s, g); break;
     }
+  } else if (six) {
+    if (MT == 1) hipLaunchKernelGGL((k_gemm<kRingDeep, 1, 6>), grid, block, 0, s, g);
+    else hipLaunchKernelGGL((k_gemm<kRingDepth, 2, 6>), grid, block, 0, s, g);
   } else if (g.wide) {
     switch (MT) {
       case 1:

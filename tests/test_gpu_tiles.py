@@ -92,3 +92,26 @@ def test_narrow_models_match_the_split_kernels_bitwise(monkeypatch, over, plan):
     assert torch.equal(got[0][1], got[1][1])
     for b in range(B):
         assert torch.equal(got[0][0][32 * b:32 * b + L], got[1][0][32 * b:32 * b + L])
+
+
+def test_gemm_widths_agree_bitwise(monkeypatch):
+    """The column blocks a GEMM workgroup takes do not change a result: a plan
+    that runs six wide (8 blocks at 16 splits of 96 blocks: 192 workgroups eight
+    wide, 256 six wide) against four
+    wide."""
+    cfg = model_config("tiny", weights_f32=False, d_model=1088, n_heads=4, n_kv_heads=2, head_dim=128, ffn_dim=1536,
+                       L=23, K=4, D=3, n_prompt=20)
+    w, prompt = setup(cfg, wseed=41, pseed=42, device="cuda")
+    dev = weights_device(w)
+    got = []
+    for plan in ("4,4,16:8,4", "4,4,16,4"):
+        print(f"case {plan}", flush=True)
+        monkeypatch.setenv("SJD_SPLITS", plan)
+        eng = make_engine(cfg, dev)
+        eng.prefill(prompt.cuda(), 3)
+        logits = torch.zeros(cfg["L"], cfg["V"], device="cuda")
+        eng.forward_window(logits)
+        torch.cuda.synchronize()
+        got.append(logits.cpu())
+        eng.close()
+    assert torch.equal(got[0], got[1])
