@@ -161,6 +161,13 @@ __global__ __launch_bounds__(256) void k_window_in(WindowIn a) {
   __shared__ float four[8][kWave];
   const int c = blockIdx.x, wave = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
   const int m = blockIdx.y * 8 + (lane >> 3), i0 = c * 256 + wave * 64 + (lane & 7) * 8;
+  if (a.st && c == 0 && blockIdx.y == 0 && threadIdx.x < kMaxStreams) {
+    const int images = a.sm.mode == kStreamsOne ? 1 : a.sm.guided ? a.sm.nz / 2 : a.sm.nz;
+    if ((int)threadIdx.x < images) {
+      a.win->n[threadIdx.x] = a.st[threadIdx.x].n;
+      a.win->n_s[threadIdx.x] = a.st[threadIdx.x].n_s;
+    }
+  }
   float s0 = 0.0f, s1 = 0.0f;
   if (m < a.M) {
     int tok, pos;

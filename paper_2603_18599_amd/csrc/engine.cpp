@@ -945,10 +945,9 @@ extern "C" int sjd_step(sjd_ctx* h, const int32_t* d_draft_tok, const float* d_d
   o.out_next = x.st->spine; o.next_stride = sstate; o.out_sib = x.st->sib; o.sib_stride = sstate;
   HIPTRY(sjd::launch_verify(a, o, s));
   const sjd::KvPlanes all{nullptr, nullptr, x.kc, x.kc_lo, x.vt, x.vt_lo, x.kv_elems};
-  HIPTRY(sjd::launch_kv_move(x.st, all, c.n_layers, c.n_kv_heads, c.head_dim, x.cap_pad, c.K, x.nstreams, x.guided,
-                             s));
   const int slot = (int)(x.steps % kRing);
-  HIPTRY(sjd::launch_state_update(x.st, d_out_meta, d_out_tok, d_out_next, c.L, x.B, x.h_n_dev + slot * x.B, s));
+  HIPTRY(sjd::launch_step_end(x.st, x.win, all, c.n_layers, c.n_kv_heads, c.head_dim, x.cap_pad, c.K, x.nstreams,
+                              x.guided, d_out_meta, d_out_tok, d_out_next, c.L, x.B, x.h_n_dev + slot * x.B, s));
   HIPTRY(hipEventRecord(x.ev[slot], s));
   x.ev_step[slot] = x.steps;
   x.steps += 1;

@@ -82,6 +82,7 @@ struct Window {
   int32_t tok[kWinRows];
   int32_t pos[kWinRows];
   uint64_t anc[kWinRows];
+  int32_t n[4], n_s[4];  // per image: cached rows and spine rows when the window was built
 };
 
 // Device-resident decoding state of one context.

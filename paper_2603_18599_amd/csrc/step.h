@@ -15,14 +15,13 @@ hipError_t launch_set_drafts(DevState* st, const int32_t* tok, int L, bool has_q
 // that stream's first pending token), or NULL
 hipError_t launch_state_init(DevState* st, const int32_t* prompt, int n_p, const int32_t* uncond, int n_u, int L,
                              int V, int vis_lo, int eol, int row_len, uint64_t seed, hipStream_t s);
-// c.kc / c.vt hold the whole caches ([layers][Hkv][...]); q planes unused.
-// ncache caches: cache z at c + z * c.sstride, driven by image z's state, or
-// (guided) caches 2b, 2b + 1 by image b's, the second at positions shifted by
-// its delta_u
-hipError_t launch_kv_move(const DevState* st, const KvPlanes& c, int layers, int Hkv, int hd, int cap, int K,
-                          int ncache, bool guided, hipStream_t s);
-// B images (states st[0..B), outputs [B][8], [B][L], [B][L]); host_n[B]:
-// pinned host memory that receives each image's cached rows (or NULL)
-hipError_t launch_state_update(DevState* st, int32_t* out_meta, int32_t* out_tok, int32_t* out_next, int L, int B,
-                               int32_t* host_n, hipStream_t s);
+// KV commit and state update after a verification. c.kc / c.vt hold the whole
+// caches ([layers][Hkv][...]); q planes unused. ncache caches: cache z at c + z *
+// c.sstride, driven by image z's state, or (guided) caches 2b, 2b + 1 by image b's,
+// the second at positions shifted by its delta_u. B images (states st[0..B), outputs
+// [B][8], [B][L], [B][L]); host_n[B]: pinned host memory that receives each
+// image's cached rows (or NULL)
+hipError_t launch_step_end(DevState* st, const Window* win, const KvPlanes& c, int layers, int Hkv, int hd, int cap,
+                           int K, int ncache, bool guided, int32_t* out_meta, int32_t* out_tok, int32_t* out_next,
+                           int L, int B, int32_t* host_n, hipStream_t s);
 }  // namespace sjd

@@ -44,64 +44,67 @@ __global__ void k_state_init(DevState* st, const int32_t* prompt, int n_p, const
   }
 }
 
-// Accepted sibling (meta[5] = k >= 2 at first rejected row r): its key and
-// value move from cache position n + n_s + r(K-1) + k-2 to n + r + 1.
-// grid (layers, Hkv, caches), block hd: cache z is the one at c + z *
-// sstride; without guidance it is image z's, with guidance caches 2b and
-// 2b + 1 are image b's text and unconditional streams (the latter's
-// positions shifted by the image's delta_u).
-__global__ void k_kv_move(const DevState* st, KvPlanes c, int Hkv, int hd, int cap, int K, int guided) {
-  const int z = blockIdx.z;
-  st += guided ? z >> 1 : z;
-  const int off = guided && (z & 1) ? st->delta_u : 0;
-  c.kc += z * c.sstride;
-  c.kc_lo += z * c.sstride;
-  c.vt += z * c.sstride;
-  c.vt_lo += z * c.sstride;
-  const int acc_k = st->meta[5];
-  if (acc_k < 2) return;
-  const int r = st->meta[1];
-  const int src = st->n + off + st->n_s + r * (K - 1) + (acc_k - 2);
-  const int dst = st->n + off + r + 1;
-  const int l = blockIdx.x, kh = blockIdx.y, j = threadIdx.x;
-  const size_t base = ((size_t)l * Hkv + kh) * cap * hd;
-  const size_t ks = base + kv_key_off(src, j, hd), kd = base + kv_key_off(dst, j, hd);
-  const size_t vs = base + kv_val_off(src, j, hd), vd = base + kv_val_off(dst, j, hd);
-  c.kc[kd] = c.kc[ks];
-  c.kc_lo[kd] = c.kc_lo[ks];
-  c.vt[vd] = c.vt[vs];
-  c.vt_lo[vd] = c.vt_lo[vs];
-}
-
-// grid B (one block per image of a batch); host_n[b] (pinned host memory)
-// receives the image's cached rows after the step
-__global__ void k_state_update(DevState* st, int32_t* out_meta, int32_t* out_tok, int32_t* out_next, int L,
-                               int32_t* host_n) {
-  __shared__ int32_t sm[8];
-  const int i = threadIdx.x, b = blockIdx.x;
-  st += b;
-  if (out_meta) out_meta += 8 * b;
-  if (out_tok) out_tok += L * b;
-  if (out_next) out_next += L * b;
-  if (i < 8) sm[i] = st->meta[i];
-  __syncthreads();
-  const int n_c = sm[0];
-  const int n_new = st->n + (n_c > 0 ? n_c : 0);
-  if (out_tok && i < L) out_tok[i] = st->tok[i];
-  if (out_next && i < L) out_next[i] = st->spine[i];
-  if (out_meta && i < 8) out_meta[i] = i == 7 ? n_new : sm[i];
-  if (host_n && i == 0) host_n[b] = n_new;
-  __syncthreads();
-  if (i == 0 && n_c > 0) {
-    st->pending = st->tok[n_c - 1];
-    st->pending_u = st->tok[n_c - 1];
-    st->n = n_new;
-    st->n_s = sm[3];
-    st->D_in = sm[2];
-    st->n_q = sm[4];
-    st->g0 = sm[6];
-    st->q_off = n_c;
-    st->meta[7] = n_new;
+// The end of a step, one launch for the KV commit and the state update (4 us
+// each on their own): the commit reads the window's cached rows and spine length
+// as they were when the window was built (win), not the state that the update
+// rewrites beside it; the outcome words it reads (meta[1], meta[5]) stay.
+// grid (layers, Hkv, caches + 1), block hd. z < caches, KV commit of cache z: an
+// accepted sibling's (meta[5] = k >= 2 at first rejected row r) key and value
+// move from cache position n + n_s + r(K-1) + k-2 to n + r + 1. Cache z is the one
+// at c + z * sstride; without guidance it is image z's, with guidance caches 2b
+// and 2b + 1 are image b's text and unconditional streams (the latter's positions
+// shifted by the image's delta_u). z = caches: state update and outputs, an image
+// per workgroup in turn; host_n[b] (pinned host memory) receives the image's
+// cached rows after the step.
+__global__ __launch_bounds__(128) void k_step_end(DevState* st, const Window* win, KvPlanes c, int Hkv, int hd,
+                                                  int cap, int K, int guided, int32_t* out_meta, int32_t* out_tok,
+                                                  int32_t* out_next, int L, int B, int32_t* host_n) {
+  const int z = blockIdx.z, j = threadIdx.x;
+  if (z + 1 < (int)gridDim.z) {
+    const int b = guided ? z >> 1 : z;
+    const DevState* s = st + b;
+    const int acc_k = s->meta[5];
+    if (acc_k < 2) return;
+    c.kc += z * c.sstride;
+    c.kc_lo += z * c.sstride;
+    c.vt += z * c.sstride;
+    c.vt_lo += z * c.sstride;
+    const int n = win->n[b] + (guided && (z & 1) ? s->delta_u : 0), r = s->meta[1];
+    const int src = n + win->n_s[b] + r * (K - 1) + (acc_k - 2);
+    const int dst = n + r + 1;
+    const size_t base = ((size_t)blockIdx.x * Hkv + blockIdx.y) * cap * hd;
+    const size_t ks = base + kv_key_off(src, j, hd), kd = base + kv_key_off(dst, j, hd);
+    const size_t vs = base + kv_val_off(src, j, hd), vd = base + kv_val_off(dst, j, hd);
+    c.kc[kd] = c.kc[ks];
+    c.kc_lo[kd] = c.kc_lo[ks];
+    c.vt[vd] = c.vt[vs];
+    c.vt_lo[vd] = c.vt_lo[vs];
+    return;
+  }
+  for (int b = blockIdx.x + gridDim.x * blockIdx.y; b < B; b += gridDim.x * gridDim.y) {
+    DevState* s = st + b;
+    // (no thread writes a word that another one reads here: meta[0..6], tok and
+    // spine stay, and n is rewritten by the thread that reads it)
+    const int n_c = s->meta[0];
+    if (out_tok && j < L) out_tok[L * b + j] = s->tok[j];
+    if (out_next && j < L) out_next[L * b + j] = s->spine[j];
+    if (out_meta && j < 7) out_meta[8 * b + j] = s->meta[j];
+    if (j == 7) {
+      const int n_new = s->n + (n_c > 0 ? n_c : 0);
+      if (out_meta) out_meta[8 * b + 7] = n_new;
+      if (host_n) host_n[b] = n_new;
+      if (n_c > 0) {
+        s->pending = s->tok[n_c - 1];
+        s->pending_u = s->tok[n_c - 1];
+        s->n = n_new;
+        s->n_s = s->meta[3];
+        s->D_in = s->meta[2];
+        s->n_q = s->meta[4];
+        s->g0 = s->meta[6];
+        s->q_off = n_c;
+        s->meta[7] = n_new;
+      }
+    }
   }
 }
 
@@ -155,14 +158,12 @@ hipError_t launch_state_init(DevState* st, const int32_t* prompt, int n_p, const
                      seed);
   return hipGetLastError();
 }
-hipError_t launch_kv_move(const DevState* st, const KvPlanes& c, int layers, int Hkv, int hd, int cap, int K,
-                          int ncache, bool guided, hipStream_t s) {
-  hipLaunchKernelGGL(k_kv_move, dim3(layers, Hkv, ncache), dim3(hd), 0, s, st, c, Hkv, hd, cap, K, guided ? 1 : 0);
-  return hipGetLastError();
-}
-hipError_t launch_state_update(DevState* st, int32_t* out_meta, int32_t* out_tok, int32_t* out_next, int L, int B,
-                               int32_t* host_n, hipStream_t s) {
-  hipLaunchKernelGGL(k_state_update, dim3(B), dim3(64), 0, s, st, out_meta, out_tok, out_next, L, host_n);
+hipError_t launch_step_end(DevState* st, const Window* win, const KvPlanes& c, int layers, int Hkv, int hd, int cap,
+                           int K, int ncache, bool guided, int32_t* out_meta, int32_t* out_tok, int32_t* out_next,
+                           int L, int B, int32_t* host_n, hipStream_t s) {
+  if (hd > 128 || hd < 64 || L > 64) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_step_end, dim3(layers, Hkv, ncache + 1), dim3(hd), 0, s, st, win, c, Hkv, hd, cap, K,
+                     guided ? 1 : 0, out_meta, out_tok, out_next, L, B, host_n);
   return hipGetLastError();
 }
 
