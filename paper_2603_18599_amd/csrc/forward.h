@@ -33,7 +33,7 @@ inline size_t act_elems(int K, int mtiles) { return (size_t)(K / 64) * mtiles * 
 
 struct GemmArgs {
   const uint16_t* A;   // activations as two bf16 planes (A = hi + lo), tiled as
-  int mtiles;          // above (rows >= M of a started tile finite)
+  int mtiles;          // above (rows >= M of a started tile may hold anything)
   int M;               // 1..128
   const uint16_t* W;   // tiled weights [N][K]
   int N, K;            // N multiple of 32, K multiple of 64

@@ -69,8 +69,8 @@ struct GemmSmem {
 // ever consumed in the step that issued it, loads are never conditional
 // (a branch makes the compiler's wait counts conservative), and within a
 // step the activation chunk is issued before the weight tile. The step count
-// is padded to a multiple of the ring: padded steps reload the last real
-// tile and stage a zero activation tile, so they add nothing.
+// is padded to a multiple of the ring: padded steps stage a zero activation
+// tile and take zero weights, so they add nothing.
 // MT = 32-row tiles of A (M <= 32 MT).
 // Workgroups are dealt to the XCDs round-robin by launch index (index i runs
 // on XCD i % kXcds). The grid is one-dimensional, and (column group, K
@@ -87,6 +87,11 @@ SJD_DEV void gemm_tile_of(int id, int groups, int splits, int& group, int& split
   split = lin / groups;
   group = lin % groups;
 }
+
+// What a padded step takes for weights, beside its zero activation tile: both
+// must be finite for the step to add nothing, and the activation buffers hold
+// whatever earlier windows left in rows that this one does not write.
+static __device__ __align__(16) uint16_t zero_tile[2048];
 
 // FOURS: the RMS scale comes from fours (narrow models' LM head); a variant of
 // its own, for its sums take 64 registers.
@@ -134,9 +139,7 @@ __global__ __launch_bounds__(NW * kWave) void k_gemm(GemmArgs g) {
   u32x4 w[kRing][4], ra[kRing][NS];
   // step t of this workgroup's range, clamped to the last real step
   auto kstep = [&](int t) { return st0 + (t < n ? t : n - 1); };
-  // steps past the range read 4 KB of the (cache-resident, finite) A plane
-  // in place of a weight tile: they are multiplied by a zero tile
-  const uint16_t* wpad = g.A + (size_t)lane * 8;
+  const uint16_t* wpad = zero_tile + (size_t)lane * 8;  // the weight tile of steps past the range
   auto issue = [&](int t, int slot) {
     const int st = kstep(t);
 #pragma unroll
