@@ -560,11 +560,11 @@ __global__ __launch_bounds__(64) void k_attn_combine(AttnArgs a) {
 
 // Attention of narrow models over short caches in one kernel: one workgroup per
 // query head and 32 slots takes two chunks at a time (8 waves, the next two's
-// tiles in flight), keeps the chunks' partials on chip and combines them, with the arithmetic and orders
-// of k_attn_partial and k_attn_combine (the same bits). What it saves is the
+// tiles in flight), keeps the chunks' partials on chip and combines them, with the
+// arithmetic and orders of k_attn_partial and k_attn_combine (the same bits). What it saves is the
 // second launch and the partials' trip through memory; its H workgroups read
-// the cache with few compute units, so it pays only while that is short
-// (kWholeChunks, at 16 heads x 64 dims).
+// the cache with few compute units, so it pays only while few positions are
+// attended (the engine's kWholeFill).
 constexpr int kWholeIters = (kWholeChunks + 1) / 2;
 template <int HD>
 struct AttnWholeSmem {

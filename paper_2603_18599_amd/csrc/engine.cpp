@@ -105,7 +105,8 @@ struct Ctx {
   // caller's stream: its kernels and arguments never change for a context
   bool use_graph = true;
   hipStream_t cap_stream = nullptr;
-  hipGraphExec_t fwd_exec[2] = {nullptr, nullptr};
+  // ([buffer][one-kernel attention]: see kWholeFill)
+  hipGraphExec_t fwd_exec[2][2] = {{nullptr, nullptr}, {nullptr, nullptr}};
   // cache-fill bound, per image: cached rows after step ev_step[i] are
   // written by the step's last kernel into h_n[i * B + b] (pinned host ring)
   int32_t* h_n = nullptr;
@@ -180,12 +181,22 @@ bool fused_shape(const sjd_config& c) {
 // (192 workgroups) on, else 4 (twice the workgroups)
 constexpr int kWideHeadV = 192 * 256;
 
+// Narrow contexts that the one-kernel attention can hold (kWholeChunks) run it
+// while a window attends to at most this many positions: one workgroup per head
+// takes two chunks at a time, and from a third on its serial chain costs more than
+// the second launch it saves (mid shape, 12 layers, 32 rows, forward in us, one
+// kernel against partial + combine; cached rows 30: 523 / 527, 90: 529 / 536, 200:
+// 527 / 556, 300: 588 / 557, 440: 598 / 560, 600: 653 / 565, 1000: 769 / 575). The
+// results have the same bits, so the host's estimate of the fill may lag.
+constexpr int kWholeFill = 2 * sjd::kAttnChunk;
+
 enum { kProjQkv = 0, kProjO = 1, kProjGu = 2, kProjDown = 3 };
 
 // Window forward of M rows: two streams (sm.mode != kStreamsOne, see
 // Streams), or one stream on the caches of stream `cache`. The rows come from
-// the decoder state, or (prefill) from prompt[n_host ..).
-int forward(Ctx& x, int M, const int32_t* prompt, const int32_t* n_dev, int n_host, float* logits,
+// the decoder state, or (prefill) from prompt[n_host ..). attend: positions that
+// the window attends to (an estimate, which decides the attention's launch shape).
+int forward(Ctx& x, int M, const int32_t* prompt, const int32_t* n_dev, int n_host, int attend, float* logits,
             const sjd::Streams& sm, int cache, hipStream_t s) {
   const sjd_config& c = x.c;
   const int d = c.d_model, H = c.n_heads, Hkv = c.n_kv_heads, hd = c.head_dim, F = c.ffn_dim;
@@ -216,7 +227,7 @@ int forward(Ctx& x, int M, const int32_t* prompt, const int32_t* n_dev, int n_ho
     a.n_dev = n_dev; a.n_host = n_host; a.M = M; a.H = H; a.Hkv = Hkv; a.cap = x.cap_pad;
     a.scale = (float)(1.4426950408889634 / std::sqrt((double)hd));
     a.ws_o = x.attn_o; a.ws_ml = x.attn_ml; a.nsplit_max = x.nsplit_max; a.out = x.att;
-    a.mtiles = mt; a.qparts = x.qparts; a.whole = x.fused ? 1 : 0;
+    a.mtiles = mt; a.qparts = x.qparts; a.whole = x.fused && attend <= kWholeFill ? 1 : 0;
     if (x.fused) {
       sjd::FusedArgs f{};
       f.mtiles = mt; f.M = M; f.inv_d = 1.0f / (float)d; f.eps = c.rms_eps;
@@ -769,7 +780,7 @@ int prefill_stream(Ctx& x, const int32_t* d_prompt, int n, int cache, hipStream_
     M = rem < P ? rem : P;
     // a last part of up to 32 rows is a window of its own: it runs the 32-row plan
     if (rem > 64 && rem <= 96) M = 64;
-    TRY(forward(x, M, d_prompt, nullptr, start, nullptr, one, cache, s));
+    TRY(forward(x, M, d_prompt, nullptr, start, start + M, nullptr, one, cache, s));
   }
   return SJD_OK;
 }
@@ -802,16 +813,32 @@ sjd::Streams window_streams(Ctx& x) {
 // window rows: one stream of L, or stream z in rows [32 z, 32 z + L)
 int window_rows(const Ctx& x) { return 32 * (x.nstreams - 1) + x.c.L; }
 
+// Positions that the next step's windows attend to, from what the host knows
+// (cache_check's state; a step that has not reported yet commits one token at least)
+int attended(const Ctx& x) {
+  long long r = 0;
+  for (int b = 0; b < x.B; ++b) {
+    const long long n = x.known_n[b] + (x.delta[b] > 0 ? x.delta[b] : 0) + (x.steps - 1 - x.known_step[b]) + x.c.L;
+    r = n > r ? n : r;
+  }
+  return (int)r;
+}
+
 // A step's window build and forward into logits buffer `buf`: replayed from
 // a graph captured on the first step that uses the buffer (the kernels read
-// every per-step value, such as n and the window, from device state).
+// every per-step value, such as n and the window, from device state) and its
+// attention's launch shape.
 int step_forward(Ctx& x, int buf, float* logits, hipStream_t s) {
   const sjd::Streams sm = window_streams(x);
+  const int attend = attended(x);
   auto enqueue = [&](hipStream_t q) -> int {
-    return forward(x, window_rows(x), nullptr, &x.st->n, 0, logits, sm, 0, q);
+    return forward(x, window_rows(x), nullptr, &x.st->n, 0, attend, logits, sm, 0, q);
   };
   if (!x.use_graph) return enqueue(s);
-  if (!x.fwd_exec[buf]) {
+  // (contexts with one launch shape keep one graph per buffer)
+  const bool two = x.fused && x.c.head_dim == 64 && x.nsplit_max <= sjd::kWholeChunks;
+  hipGraphExec_t& exec = x.fwd_exec[buf][two && attend <= kWholeFill ? 1 : 0];
+  if (!exec) {
     hipGraph_t g = nullptr;
     HIPTRY(hipStreamBeginCapture(x.cap_stream, hipStreamCaptureModeRelaxed));
     const int rc = enqueue(x.cap_stream);
@@ -820,14 +847,14 @@ int step_forward(Ctx& x, int buf, float* logits, hipStream_t s) {
       if (g) (void)hipGraphDestroy(g);
       return rc != SJD_OK ? rc : SJD_EHIP;
     }
-    const hipError_t ei = hipGraphInstantiate(&x.fwd_exec[buf], g, nullptr, nullptr, 0);
+    const hipError_t ei = hipGraphInstantiate(&exec, g, nullptr, nullptr, 0);
     (void)hipGraphDestroy(g);
     if (ei != hipSuccess) {
-      x.fwd_exec[buf] = nullptr;
+      exec = nullptr;
       return SJD_EHIP;
     }
   }
-  HIPTRY(hipGraphLaunch(x.fwd_exec[buf], s));
+  HIPTRY(hipGraphLaunch(exec, s));
   return SJD_OK;
 }
 
@@ -970,7 +997,7 @@ extern "C" int sjd_forward_window(sjd_ctx* h, float* d_logits, void* stream) {
   TRY(cache_check(x));
   hipStream_t s = (hipStream_t)stream;
   const sjd::Streams sm = window_streams(x);
-  return forward(x, window_rows(x), nullptr, &x.st->n, 0, d_logits, sm, 0, s);
+  return forward(x, window_rows(x), nullptr, &x.st->n, 0, attended(x), d_logits, sm, 0, s);
 }
 
 extern "C" int sjd_get_plan(const sjd_ctx* h, int32_t* splits, int32_t n) {
@@ -993,8 +1020,9 @@ extern "C" void sjd_destroy(sjd_ctx* h) {
   if (!h) return;
   Ctx& x = h->x;
   (void)hipDeviceSynchronize();
-  for (hipGraphExec_t& e : x.fwd_exec)
-    if (e) (void)hipGraphExecDestroy(e);
+  for (auto& per_buf : x.fwd_exec)
+    for (hipGraphExec_t e : per_buf)
+      if (e) (void)hipGraphExecDestroy(e);
   if (x.cap_stream) (void)hipStreamDestroy(x.cap_stream);
   for (void* p : x.owned) (void)hipFree(p);
   if (x.h_n) (void)hipHostFree(x.h_n);

@@ -167,11 +167,14 @@ struct AttnArgs {
   int nsplit_max;
   uint16_t* out;         // tiled activations (act_off), `mtiles` row tiles
   int mtiles;
-  int whole;             // 64-dim heads, at most kWholeChunks chunks of capacity: one kernel
+  int whole;             // one kernel, where it can hold the cache (64-dim heads, kWholeChunks)
   int qparts;            // workgroups per key / value head, each taking H / Hkv / qparts query heads
 };
 constexpr int kAttnChunk = 128;  // keys per workgroup (4 waves x 32)
-constexpr int kWholeChunks = 4;  // k_attn_whole: chunks of a cache, at most (and no more than kCombGroup)
+// k_attn_whole: chunks that its shared memory holds (no more than kCombGroup, whose
+// order of sums it keeps). On the capacity, which no fill exceeds: what a captured
+// launch holds is right for every later fill.
+constexpr int kWholeChunks = 4;
 hipError_t launch_attention(const AttnArgs& a, int hd, hipStream_t s);
 
 // elementwise kernels

@@ -94,6 +94,39 @@ def test_narrow_models_match_the_split_kernels_bitwise(monkeypatch, over, plan):
         assert torch.equal(got[0][0][32 * b:32 * b + L], got[1][0][32 * b:32 * b + L])
 
 
+@pytest.mark.parametrize("n_prompt,batch", [(215, 1), (215, 2), (250, 1)])
+def test_attention_launch_shape_follows_the_fill_bitwise(monkeypatch, n_prompt, batch):
+    """Narrow contexts of at most 512 positions attend in one kernel while the
+    fill is short and in two beyond: a generation that crosses the line, in
+    prefill or between steps (each step synchronised, so that the host knows the
+    fill; a second image far behind the first), against the split kernels."""
+    from paper_2603_18599_amd.sjd import SJD_AC, SJD_PD, SJD_TUNE
+    monkeypatch.setenv("SJD_SPLITS", "4,4,4,4")
+    base = model_config("tiny", weights_f32=False, d_model=512, n_heads=8, n_kv_heads=4, ffn_dim=1024, vocab_size=1056,
+                        V=1056, L=32, K=4, D=3, n_prompt=n_prompt, batch=batch, max_seq=512)
+    w, prompt = setup(base, wseed=61, pseed=62, device="cuda")
+    dev = weights_device(w)
+    got = []
+    for flags in (SJD_AC | SJD_PD, SJD_AC | SJD_PD | SJD_TUNE):
+        print(f"prompt {n_prompt} batch {batch} flags {flags}", flush=True)
+        eng = make_engine(dict(base, flags=flags), dev)
+        for again in range(2):  # the second generation starts below the line again
+            for b in range(batch):
+                eng.prefill_image(b, prompt[:n_prompt - 100 * b].cuda(), 5 + b)
+            logits = torch.zeros(32 * batch, base["V"], device="cuda")
+            meta = torch.zeros(batch, 8, dtype=torch.int32, device="cuda")
+            for t in range(24):
+                eng.step(1.0, 8, 5, t, out_meta=meta)
+                torch.cuda.synchronize()
+                got.append(meta.cpu())
+            eng.forward_window(logits)
+            got.append(logits.cpu())
+            assert int(meta[0, 7]) + 32 > 256  # (cached rows plus the window)
+        eng.close()
+    half = len(got) // 2
+    assert all(torch.equal(a, b) for a, b in zip(got[:half], got[half:]))
+
+
 def test_gemm_widths_agree_bitwise(monkeypatch):
     """The column blocks a GEMM workgroup takes do not change a result: a plan
     that runs six wide (8 blocks at 16 splits of 96 blocks: 192 workgroups eight
