@@ -380,6 +380,7 @@ Ctx::Plan tune_projection(Ctx& x, int proj, const std::vector<Ctx::Plan>& cand, 
   const int d = c.d_model, H = c.n_heads, Hkv = c.n_kv_heads, hd = c.head_dim, F = c.ffn_dim;
   const int Nq = H * hd, Nkv = Hkv * hd, Nqkv = Nq + 2 * Nkv;
   const Ctx::Plan fail{0, 0};
+  const int mt = (M + 31) / 32;  // row tiles of the activations, as in forward()
   const size_t qplane = (size_t)x.Mpad * Nqkv, rplane = (size_t)x.Mpad * d, guplane = (size_t)x.Mpad * 2 * F;
   const sjd::Streams one{sjd::kStreamsOne, 0, 0, 0, nullptr};
   auto pair = [&](const Ctx::Plan& pl, int rep) -> hipError_t {
@@ -389,7 +390,7 @@ Ctx::Plan tune_projection(Ctx& x, int proj, const std::vector<Ctx::Plan>& cand, 
     g.M = M; g.S = S; g.wide = pl.wide;
     if (proj == kProjQkv || proj == kProjGu) {
       g.ss = x.ss; g.ss_n = sjd::norm_chunks(d); g.inv_d = 1.0f / (float)d; g.eps = c.rms_eps;
-      g.A = x.xn; g.mtiles = x.mtiles; g.K = d;
+      g.A = x.xn; g.mtiles = mt; g.K = d;
     }
     hipError_t e;
     switch (proj) {
@@ -400,19 +401,19 @@ Ctx::Plan tune_projection(Ctx& x, int proj, const std::vector<Ctx::Plan>& cand, 
         return sjd::launch_rope_kv(x.qkv, S, qplane, x.win, nullptr, 0, M, H, Hkv, hd, x.rope, kv, x.cap_pad, one, s);
       }
       case kProjO:
-        g.A = x.att; g.mtiles = x.mtiles; g.W = w[4]; g.N = d; g.K = Nq;
+        g.A = x.att; g.mtiles = mt; g.W = w[4]; g.N = d; g.K = Nq;
         g.out = x.rpart; g.plane = rplane; g.ldo = d;
         if ((e = sjd::launch_gemm(g, s)) != hipSuccess) return e;
-        return sjd::launch_resid_norm(x.x, x.rpart, S, rplane, w[5], M, d, x.xn, x.mtiles, x.ss, nullptr, s);
+        return sjd::launch_resid_norm(x.x, x.rpart, S, rplane, w[5], M, d, x.xn, mt, x.ss, nullptr, s);
       case kProjGu:
         g.W = w[6]; g.N = 2 * F; g.out = x.gup; g.plane = guplane; g.ldo = 2 * F;
         if ((e = sjd::launch_gemm(g, s)) != hipSuccess) return e;
-        return sjd::launch_swiglu(x.gup, S, guplane, M, F, x.hbuf, x.mtiles, s);
+        return sjd::launch_swiglu(x.gup, S, guplane, M, F, x.hbuf, mt, s);
       default:
-        g.A = x.hbuf; g.mtiles = x.mtiles; g.W = w[8]; g.N = d; g.K = F;
+        g.A = x.hbuf; g.mtiles = mt; g.W = w[8]; g.N = d; g.K = F;
         g.out = x.rpart; g.plane = rplane; g.ldo = d;
         if ((e = sjd::launch_gemm(g, s)) != hipSuccess) return e;
-        return sjd::launch_resid_norm(x.x, x.rpart, S, rplane, w[0], M, d, x.xn, x.mtiles, x.ss, nullptr, s);
+        return sjd::launch_resid_norm(x.x, x.rpart, S, rplane, w[0], M, d, x.xn, mt, x.ss, nullptr, s);
     }
   };
   hipEvent_t e0 = nullptr, e1 = nullptr;
