@@ -340,9 +340,9 @@ SJD_API int sjd_forward_window(sjd_ctx* ctx, float* d_logits, void* stream);
 /* The context's GEMM plan, written to splits[0 .. min(n, 20)): for windows
  * of up to 32 rows, [0..5) how many workgroups share the K range of the
  * QKV, O, gate|up, down and LM-head projections and [5..10) how many 32-column
- * blocks each workgroup takes (4 or 8; where 8 would leave compute units idle
- * the kernel runs 6, with the same results); [10..20) the same for windows of
- * more rows (several streams, L > 32, prefill). Chosen at sjd_init (see
+ * blocks each workgroup takes (4 or 8; at up to 64 rows, where 8 would leave
+ * compute units idle, the kernel may run 6, with the same results); [10..20) the
+ * same for windows of more rows (several streams, L > 32, prefill). Chosen at sjd_init (see
  * SJD_TUNE): the plan recorded for the shape, else the closed form; with
  * SJD_TUNE the process-wide timed plan; and, when the environment variable
  * SJD_SPLITS="qkv,o,gu,down" is set (each entry S or S:blocks), that plan for

@@ -100,6 +100,7 @@ struct Ctx {
   // attention workgroups per key / value head (its grouped query heads split
   // over them)
   int qparts = 1;
+  int ncu = 256;  // the device's compute units
   // the step's window forward (window build + ~10 kernels per layer + head),
   // captured once per logits buffer on cap_stream and replayed on the
   // caller's stream: its kernels and arguments never change for a context
@@ -213,6 +214,7 @@ int forward(Ctx& x, int M, const int32_t* prompt, const int32_t* n_dev, int n_ho
   // summation order does not depend on its window)
   const Ctx::Plan* P = M > 64 && !prompt ? x.plan_wide : x.plan[M > 32 ? 1 : 0];
   sjd::GemmArgs normed{};  // GEMM arguments that apply the RMSNorm row scale
+  normed.ncu = x.ncu;
   normed.ss = x.ss;
   normed.ss_n = sjd::norm_chunks(d);
   normed.inv_d = 1.0f / (float)d;
@@ -245,7 +247,7 @@ int forward(Ctx& x, int M, const int32_t* prompt, const int32_t* n_dev, int n_ho
           return SJD_OK;
         }
         sjd::GemmArgs g{};
-        g.A = A; g.mtiles = mt; g.M = M; g.W = W; g.N = d; g.K = K; g.S = S; g.wide = wide;
+        g.ncu = x.ncu; g.A = A; g.mtiles = mt; g.M = M; g.W = W; g.N = d; g.K = K; g.S = S; g.wide = wide;
         g.out = x.rpart; g.plane = rplane; g.ldo = d;
         HIPTRY(sjd::launch_gemm(g, s));
         HIPTRY(sjd::launch_resid_norm(x.x, x.rpart, S, rplane, gain, M, d, x.xn, mt, nullptr, x.fours, s));
@@ -267,7 +269,7 @@ int forward(Ctx& x, int M, const int32_t* prompt, const int32_t* n_dev, int n_ho
                                sm, s));
     HIPTRY(sjd::launch_attention(a, hd, s));
     g = sjd::GemmArgs{};
-    g.A = x.att; g.mtiles = mt; g.M = M; g.W = w[4]; g.N = d; g.K = Nq; g.S = P[kProjO].S;
+    g.ncu = x.ncu; g.A = x.att; g.mtiles = mt; g.M = M; g.W = w[4]; g.N = d; g.K = Nq; g.S = P[kProjO].S;
     g.wide = P[kProjO].wide; g.out = x.rpart; g.plane = rplane; g.ldo = d;
     HIPTRY(sjd::launch_gemm(g, s));
     HIPTRY(sjd::launch_resid_norm(x.x, x.rpart, P[kProjO].S, rplane, w[5], M, d, x.xn, mt, x.ss, nullptr, s));
@@ -277,7 +279,7 @@ int forward(Ctx& x, int M, const int32_t* prompt, const int32_t* n_dev, int n_ho
     HIPTRY(sjd::launch_gemm(g, s));
     HIPTRY(sjd::launch_swiglu(x.gup, P[kProjGu].S, guplane, M, F, x.hbuf, mt, s));
     g = sjd::GemmArgs{};
-    g.A = x.hbuf; g.mtiles = mt; g.M = M; g.W = w[8]; g.N = d; g.K = F; g.S = P[kProjDown].S;
+    g.ncu = x.ncu; g.A = x.hbuf; g.mtiles = mt; g.M = M; g.W = w[8]; g.N = d; g.K = F; g.S = P[kProjDown].S;
     g.wide = P[kProjDown].wide; g.out = x.rpart; g.plane = rplane; g.ldo = d;
     HIPTRY(sjd::launch_gemm(g, s));
     pend = P[kProjDown].S;
@@ -387,7 +389,7 @@ Ctx::Plan tune_projection(Ctx& x, int proj, const std::vector<Ctx::Plan>& cand, 
     const auto& w = x.lw[rep % c.n_layers];
     const int S = pl.S;
     sjd::GemmArgs g{};
-    g.M = M; g.S = S; g.wide = pl.wide;
+    g.ncu = x.ncu; g.M = M; g.S = S; g.wide = pl.wide;
     if (proj == kProjQkv || proj == kProjGu) {
       g.ss = x.ss; g.ss_n = sjd::norm_chunks(d); g.inv_d = 1.0f / (float)d; g.eps = c.rms_eps;
       g.A = x.xn; g.mtiles = mt; g.K = d;
@@ -596,13 +598,13 @@ extern "C" int sjd_init(const sjd_config* cfg, const sjd_weights* w, void* strea
   // split-K plan: the closed form aims for two to three workgroups per
   // compute unit; unless SJD_NO_TUNE, the process-wide tuned plan replaces it
   // (tuned below, by the first context that meets a shape)
-  int ncu = 256;
   {
     int dev = 0;
     hipDeviceProp_t prop;
     if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess)
-      ncu = prop.multiProcessorCount;
+      x.ncu = prop.multiProcessorCount;
   }
+  const int ncu = x.ncu;
   const int target = 5 * ncu / 2;
   // grouped-query attention: one attention workgroup per query head by
   // default (the parts of a key / value head share an XCD and its L2, so the

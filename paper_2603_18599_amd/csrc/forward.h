@@ -53,9 +53,11 @@ struct GemmArgs {
   int cfg_rows;
   float cfg_w;
   // 8 column blocks per workgroup (else 4): half the activation loads per weight
-  // byte; the grid is N / 256 column groups x S. (launch_gemm runs it 6 wide where
-  // that fills more compute units; the width does not change a result.)
+  // byte; the grid is N / 256 column groups x S. (launch_gemm runs it 6 wide at up
+  // to 64 rows where 8 would leave compute units idle; the width does not change a
+  // result.)
   int wide;
+  int ncu;  // the device's compute units
 };
 
 // splits for about target_wgs workgroups of 4 (or, wide, 8) column blocks

@@ -251,26 +251,34 @@ int gemm_splits(int N, int K, int target_wgs, bool wide) {
 }
 
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
-  if (g.M < 1 || g.M > 128 || g.M > 32 * g.mtiles || g.N % 32 || g.K % 64 || g.S < 1 || g.S > kGemmMaxSplits) return hipErrorInvalidValue;
+  if (g.M < 1 || g.M > 128 || g.M > 32 * g.mtiles || g.N % 32 || g.K % 64 || g.S < 1 || g.S > kGemmMaxSplits ||
+      g.ncu < 1)
+    return hipErrorInvalidValue;
   const int MT = (g.M + 31) / 32;
   if (g.fours && (g.ss || g.ss_n > kFusedMaxChunks)) return hipErrorInvalidValue;
   if (g.cfg_rows < 0 || g.cfg_rows > 32 || (g.cfg_rows > 0 && (MT & 1))) return hipErrorInvalidValue;
-  // Eight blocks wide, a grid well short of one workgroup per compute unit leaves
-  // the others idle, and one unit does not draw more than about 55 GB/s: six wide
-  // if that still is at most one each (7B gate | up at 2 splits: 172 -> 230
-  // workgroups; with its consumer 36.4 -> 34.2 us at 32 rows, 44.7 -> 43.3 at 64; at 128 rows the step
-  // lost 2%)
+  // Eight blocks wide, a grid short of one workgroup per compute unit leaves the
+  // others idle, and one unit does not draw more than about 55 GB/s: six wide from
+  // three quarters of the units down, if that grid still is at most one each. At 32
+  // rows that pays however small the grid (six layers of the 7B shape, QKV / gate |
+  // up / down at 48 / 86 / 16 workgroups eight wide: forward 1617 -> 1418 us; 96 / 86
+  // / 96 975 -> 904; 144 / 172 / 128 794 -> 759, gate | up six wide in both; alone,
+  // 172 -> 230 workgroups, 36.4 -> 34.2 with its consumer). At 64 rows only if it
+  // then fills more than three quarters (172 -> 230 44.7 -> 43.3 us; the O projection
+  // of a d = 2048 model, 128 -> 176, lost 0.4% of a 12-layer forward), at 128 rows
+  // not (the 7B step lost 2%).
   const auto groups = [&](int w) { return (g.N / 32 + w - 1) / w * g.S; };
-  const bool six = g.wide && !g.fours && MT <= 2 && groups(kGWavesWide) <= 192 && groups(6) > 192 && groups(6) <= 256;
+  const bool six = g.wide && !g.fours && MT <= 2 && 4 * groups(kGWavesWide) <= 3 * g.ncu && groups(6) <= g.ncu &&
+                   (MT == 1 || 4 * groups(6) > 3 * g.ncu);
   const int nw = six ? 6 : g.wide ? kGWavesWide : kGWaves;
   const dim3 grid((unsigned)(((g.N / 32 + nw - 1) / nw) * g.S)), block((unsigned)(nw * kWave));
   // at one workgroup per compute unit or fewer nothing else hides a
   // workgroup's load latency: keep more weight tiles in flight
-  const bool lone = grid.x <= 256;
+  const bool lone = (int)grid.x <= g.ncu;
   // 8 waves have half of that latency covered among themselves: deeper only where
   // compute units stay idle (32 rows, gate | up 172 workgroups 34.3 -> 33.0 us; QKV
   // 240 20.0 -> 21.3, and at 64 rows 23.2 -> 31, LM head 81 -> 108)
-  const bool sparse = grid.x <= 192;
+  const bool sparse = 4 * (int)grid.x <= 3 * g.ncu;
   if (g.fours && !g.wide && MT == 1) {
     hipLaunchKernelGGL((k_gemm<kRingDeep, 1, kGWaves, true>), grid, block, 0, s, g);
   } else if (g.fours && !g.wide) {

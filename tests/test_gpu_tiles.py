@@ -148,3 +148,32 @@ def test_gemm_widths_agree_bitwise(monkeypatch):
         got.append(logits.cpu())
         eng.close()
     assert torch.equal(got[0], got[1])
+
+
+@pytest.mark.parametrize("plan", ["3:8,2:8,1:8,3:8", "9:8,32:8,16:8,32:8", "1:8,1,3:8,1:8", "7,3:8,5,11:8"])
+def test_wide_groups_with_idle_waves_on_wide_models(orc, monkeypatch, plan):
+    """As test_window_forward_wide_groups_with_idle_waves, on a model that is not
+    narrow, so that every projection is a GEMM of its own: QKV 180 blocks, O and down
+    34, gate|up 100, none a multiple of 8 (O, down and gate|up not of 6 either).
+    Grids of more than 192 workgroups run eight wide (QKV at 9 splits, gate|up at 16),
+    the smaller ones six; 17 k-steps, fewer than some splits."""
+    cfg = model_config("tiny", weights_f32=False, n_layers=2, d_model=1088, n_heads=39, n_kv_heads=3, head_dim=128,
+                       ffn_dim=1600, L=32, K=4, D=3, n_prompt=9)
+    w, prompt = setup(cfg, wseed=71, pseed=72, device="cuda")
+    dev = weights_device(w)
+    got = []
+    for pin in (plan, plan.replace(":8", "")):
+        print(f"case {pin}", flush=True)
+        monkeypatch.setenv("SJD_SPLITS", pin)
+        eng = make_engine(cfg, dev)
+        eng.prefill(prompt.cuda(), 7)
+        logits = torch.empty(cfg["L"], cfg["V"], dtype=torch.float32, device="cuda")
+        eng.forward_window(logits)
+        torch.cuda.synchronize()
+        got.append(logits.cpu())
+        eng.close()
+    assert torch.equal(got[0], got[1])  # the width does not change a result
+    ref = oracle_first_window(orc, cfg, weights_numpy(w), prompt.numpy().astype(np.int32), 7)
+    err = np.abs(got[0].numpy() - ref).max()
+    print(f"max |logit error| = {err:.3e}, max |logit| = {np.abs(ref).max():.3f}", flush=True)
+    assert err <= np.abs(ref).max() * 2.0 ** -11, err
