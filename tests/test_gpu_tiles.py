@@ -177,3 +177,32 @@ def test_wide_groups_with_idle_waves_on_wide_models(orc, monkeypatch, plan):
     err = np.abs(got[0].numpy() - ref).max()
     print(f"max |logit error| = {err:.3e}, max |logit| = {np.abs(ref).max():.3f}", flush=True)
     assert err <= np.abs(ref).max() * 2.0 ** -11, err
+
+
+@pytest.mark.parametrize("L,batch", [(1, 1), (32, 1), (33, 1), (20, 3), (32, 4)])
+def test_narrow_models_with_a_wide_head_match_the_split_kernels_bitwise(monkeypatch, L, batch):
+    """The LM head of a narrow model with many columns: eight blocks per workgroup,
+    its row scale from the sums of squares of fours of columns; 1539 blocks, so that
+    the last workgroup has idle waves; one to four row tiles. Against the split
+    kernels (the LM head's row scale from chunk sums) under the same plan."""
+    from paper_2603_18599_amd.sjd import SJD_AC, SJD_PD, SJD_TUNE
+    monkeypatch.setenv("SJD_SPLITS", "3,2,4,5")
+    base = model_config("tiny", weights_f32=False, n_layers=1, d_model=320, n_heads=5, n_kv_heads=5, ffn_dim=640,
+                        vocab_size=49248, V=49248, L=L, K=1, D=0, n_prompt=40, batch=batch)
+    w, prompt = setup(base, wseed=81, pseed=82, device="cuda")
+    dev = weights_device(w)
+    got = []
+    for flags in (SJD_AC | SJD_PD, SJD_AC | SJD_PD | SJD_TUNE):
+        print(f"L {L} batch {batch} flags {flags}", flush=True)
+        eng = make_engine(dict(base, flags=flags), dev)
+        assert eng.plan()[9] == 8
+        for b in range(batch):
+            eng.prefill_image(b, prompt[:len(prompt) - b].cuda(), 5 + b)
+        logits = torch.zeros(32 * (batch - 1) + L, base["V"], device="cuda")
+        eng.forward_window(logits)
+        torch.cuda.synchronize()
+        got.append(logits.cpu())
+        eng.close()
+    for b in range(batch):
+        assert torch.isfinite(got[0][32 * b:32 * b + L]).all()
+        assert torch.equal(got[0][32 * b:32 * b + L], got[1][32 * b:32 * b + L])
