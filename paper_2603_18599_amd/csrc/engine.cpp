@@ -170,10 +170,13 @@ int check_config(const sjd_config* c) {
 // workgroup of such a projection reads the whole activation, 128 bytes per k and
 // row tile, so the line lies where that stops being cheap beside the launch it
 // saves: see fused.hip.
-// Their residual projections are one kernel up to K = 1024 (7.0 us at d = 1024,
-// where GEMM and norm take 11.2); at K = 2816 the 32 workgroups' 540 KB each
-// arrive too slowly (13.8 us against 11.8).
-constexpr int kFusedResidK = 1536;
+// Their residual projections are one kernel up to this K: all of it passes through
+// each of the d / 32 workgroups (128 bytes of activations and 64 of weights per k),
+// while the split GEMM spreads it. Whole forwards of 8 layers at d = 1024, 32 rows,
+// split -> one kernel: K 1536 (O and down) 348 -> 295 us, 2048 314 -> 298, 2304 321 ->
+// 305, 2560 322 -> 311; 2816, with a plan timed for the split kernels, 330 -> 327-343
+// (down alone 11.8 -> 13.8). At 128 rows 11% faster at 2048 to 2560, 7% at 2816.
+constexpr int kFusedResidK = 2560;
 bool fused_shape(const sjd_config& c) {
   return sjd::norm_chunks(c.d_model) <= sjd::kFusedMaxChunks && c.n_heads * c.head_dim <= 4096 && c.ffn_dim <= 4096;
 }

@@ -58,6 +58,8 @@ NARROW = [
     (dict(d_model=960, n_heads=15, n_kv_heads=15, ffn_dim=2816, L=32, K=4, D=3, n_prompt=64, batch=4), "8,8,5,22"),
     (dict(d_model=512, n_heads=8, n_kv_heads=4, ffn_dim=1024, L=20, K=4, D=3, n_prompt=200, cfg_w=3.0), "3,32,17,31"),
     (dict(d_model=256, n_heads=4, n_kv_heads=4, ffn_dim=1024, L=64, K=4, D=3, n_prompt=470, max_seq=1000), "2,2,2,4"),
+    (dict(d_model=448, n_heads=7, n_kv_heads=7, ffn_dim=2560, L=25, K=4, D=3, n_prompt=135), "3,5,2,31"),
+    (dict(d_model=384, n_heads=41, n_kv_heads=1, ffn_dim=2624, L=26, K=4, D=3, n_prompt=135), "3,9,2,13"),
 ]
 
 
