@@ -35,7 +35,10 @@ SJD_DEV void add_planes(float (&acc)[C], const float* p, int S, size_t plane) {
 // lane = (row % 8) * 8 + column / C. With C = 8 a wave reads 256 contiguous bytes
 // of each row and writes whole 128-byte lines (8 rows x 16 bytes) of the tile;
 // C = 4 spreads narrow matrices over twice the waves (two of them share a
-// line): at d = 1024 and 22 planes C = 8 took 5.2 us where C = 4 takes 4.2.
+// line): at d = 1024 and 22 planes C = 8 took 5.2 us where C = 4 takes 4.2. Whole
+// forwards of two images, C = 8 -> 4 in the norm at 256 waves (d = 2048, 12 layers)
+// 1245 -> 1229 us, at 384 (d = 3072, 8 layers) 1102 -> 1090; one 8B image of 6 layers
+// (256) 736 -> 731; the 7B shape 734 either way.
 constexpr int kNarrowWaves = 512;  // C = 4 where C = 8 would give fewer waves
 
 // x += sum_s part[s] (split-K partial planes of the projection that feeds
@@ -103,7 +106,7 @@ hipError_t launch_resid_norm(float* x, const float* part, int S, size_t plane, c
                              : k_resid_norm<kGemmMaxSplits, C>;
     hipLaunchKernelGGL(k, grid, dim3(2048 / C), 0, s, x, part, S, plane, g, M, d, y, mtiles, ss, fours);
   };
-  if ((d / 64) * ((M + 7) / 8) < kNarrowWaves / 2) go(std::integral_constant<int, 4>{});
+  if ((d / 64) * ((M + 7) / 8) < kNarrowWaves) go(std::integral_constant<int, 4>{});
   else go(std::integral_constant<int, 8>{});
   return hipGetLastError();
 }
