@@ -79,7 +79,10 @@ typedef enum {
  * process that meets a projection shape times GEMM + consumer pairs; every
  * later context of the process reuses its choice): possibly faster on other
  * shapes, but the choice depends on timing, so two processes may round
- * differently. SJD_NO_TUNE forces the closed form. */
+ * differently. Not for narrow models (d_model <= 1024, n_heads * head_dim and
+ * ffn_dim <= 4096): by default they run each projection and its consumer as one
+ * kernel, SJD_TUNE runs the two kernels that it times, and these are slower
+ * (1.1 to 2 times per forward). SJD_NO_TUNE forces the closed form. */
 #define SJD_NO_TUNE 8u
 #define SJD_TUNE 16u
 /* debug: check every logits row a verification reads for NaN and +inf first
@@ -342,7 +345,10 @@ SJD_API int sjd_forward_window(sjd_ctx* ctx, float* d_logits, void* stream);
  * QKV, O, gate|up, down and LM-head projections and [5..10) how many 32-column
  * blocks each workgroup takes (4 or 8; at up to 64 rows, where 8 would leave
  * compute units idle, the kernel may run 6, with the same results); [10..20) the
- * same for windows of more rows (several streams, L > 32, prefill). Chosen at sjd_init (see
+ * same for windows of more rows (several streams, L > 32, prefill). A narrow
+ * model's context (see SJD_TUNE) takes the splits, which set the summation
+ * order, but one block per workgroup and no split grid in QKV, gate|up and, at
+ * up to 2560 inputs, O and down, whatever the widths say. Chosen at sjd_init (see
  * SJD_TUNE): the plan recorded for the shape, else the closed form; with
  * SJD_TUNE the process-wide timed plan; and, when the environment variable
  * SJD_SPLITS="qkv,o,gu,down" is set (each entry S or S:blocks), that plan for
