@@ -44,7 +44,7 @@ struct Ctx {
   std::vector<void*> owned;
   // activations entering GEMMs are tiled hi / lo bf16 planes (forward.h); q is
   // row-major, hi and lo planes
-  int mtiles = 2;  // Mpad / 32
+  int mtiles = kPrefillRows / 32;  // Mpad / 32
   float* x = nullptr;
   uint16_t* xn = nullptr;
   float* qkv = nullptr;
@@ -85,7 +85,8 @@ struct Ctx {
   int32_t* nonfinite = nullptr;  // SJD_CHECK_FINITE: count of NaN / +inf logits found
   // GEMM plan per projection (QKV, O, gate|up, down): split count and column
   // blocks per workgroup, for windows of <= 32 rows [0] and of more [1]
-  // (two streams, L > 32, prefill windows); the LM head runs wide, unsplit
+  // (two streams, L > 32, prefill windows); the LM head runs unsplit (its width:
+  // kWideHeadV)
   struct Plan {
     int S = 1, wide = 0;
   };
@@ -182,7 +183,10 @@ bool fused_shape(const sjd_config& c) {
 }
 
 // The LM head (unsplit) takes 8 column blocks per workgroup from this many columns
-// (192 workgroups) on, else 4 (twice the workgroups)
+// (192 workgroups) on, else 4 (twice the workgroups). Forwards of two 8B layers and
+// the head (32768 columns), 8 -> 4 blocks: 32 rows 283 -> 269 us, 64 344 -> 328, 96 407 ->
+// 401, 128 499 -> 481; of two mid layers (16384 columns) 101 -> 96, 121 -> 118, 149 -> 147,
+// 167 -> 163. At 65536 columns 8 blocks fill the compute units once (32 rows 8% faster).
 constexpr int kWideHeadV = 192 * 256;
 
 // Narrow contexts that the one-kernel attention can hold (kWholeChunks) run it

@@ -18,6 +18,11 @@
 // for 5.2 + 4.8) a 12-layer step at short caches 643 -> 590 us, the start of an
 // image (prompt 64, 8 steps) 6.87 -> 5.65 ms; d = 256, 2 layers, 16 steps 2.16 ->
 // 1.43 ms.
+// A second row tile reads the weights again, from the caches; it pays all the same.
+// Forwards at 200 cached rows, split kernels -> fused: mid shape (12 layers) 32 rows
+// 635 -> 531 us, 64 768 -> 637, 96 868 -> 782, 128 1018 -> 851; d = 512 (12 layers) 555 -> 370
+// and at 128 rows 868 -> 419; d = 1024 with an FFN of 4096 (6 layers) 340 -> 256 and 544 ->
+// 453. Prompts of 500 (128-row windows): mid 3841 -> 3190, d = 512 3320 -> 1610.
 // Columns whose results meet in one epilogue share a block: block b of the q,
 // k, v rows holds 16 dims of a head and the 16 they rotate with, block b of gate |
 // up holds 16 gate columns and the same 16 of up.

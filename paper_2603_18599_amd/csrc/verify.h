@@ -14,7 +14,9 @@ constexpr uint32_t kFlagDraftStats = 1u << 28;  // (internal) draft statistics a
 // Launches of at most this many rows hold target and draft row of a window row
 // in one workgroup (see launch_verify)
 constexpr long two_row_rows(int V) { return V > 4096 && V <= 16384 ? 1280 : 512; }
-constexpr int kRecInts = 16;  // per-row record: tok, stage, 7 drafting candidates, fresh, pad
+// per-row record: tok, stage, 7 drafting candidates, fresh, pad (until the row kernel
+// writes it, words 0..6 may hold its draft row's statistics, see k_draft_stats)
+constexpr int kRecInts = 16;
 constexpr int kVerifyMaxV = 65536;  // logits per row held on chip
 constexpr int kVerifyMaxK = 2048;   // kept (top-k) tokens per row when V > kVerifyMaxK
 

@@ -1386,13 +1386,6 @@ SJD_DEV double softmax_weights(float* w, int n, float m, float T, Sh& sh) {
   return 1.0 / block_sum_d<W>(z, sh.red_d);
 }
 
-template <int BLOCK, int NC, class Sh>
-SJD_DEV bool kept(const Sh& sh, int x) { return (sh.bm[x >> 5] >> (x & 31)) & 1u; }
-template <int BLOCK, int NC, class Sh>
-SJD_DEV int rank_of(const Sh& sh, int x) {
-  return sh.pre[x >> 5] + __popc(sh.bm[x >> 5] & ((1u << (x & 31)) - 1u));
-}
-
 struct Stages {
   int n;        // stages whose residual has been formed
   int cand[8];
@@ -2065,7 +2058,12 @@ SJD_DEV void verify_row(const VerifyArgs& a, VSh<BLOCK, NC, TWO>& sh, int b, int
 
 // One workgroup per row, grid (window rows, trials). TWO: both rows in
 // registers, two 512-thread workgroups to a compute unit; otherwise the target
-// row alone.
+// row alone, three to a unit (of 1024 threads two, at more than 32768 logits one).
+// Those register limits (80, 64 and 128) spill 16, 48 and 80 vector registers, and
+// 1024 threads with two rows 16: the whole-row selection is compiled into the same
+// kernel as the candidate path that decides almost every row. More workgroups are
+// worth it: without spills at 128 registers the 131072 rows of 16384 logits took
+// 5417 us for 4350, 2048 rows 132 for 113, 16384 rows of 32768 logits 1578 for 1189.
 template <int BLOCK, int NC, bool TWO>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(BLOCK < 512 ? 1 : TWO || NC > 8 ? 4 : BLOCK > 512 ? 8 : 6)))
 void k_verify_rows(VerifyArgs a) {
