@@ -197,6 +197,11 @@ def calibration_copy():
     del a, b
 
 
+# (decoder step, verification): the kernel that a launch has once (a step: its
+# first), and (verification) the names of a launch's kernels
+LAUNCH_KERNELS = (("k_window_in", ()), ("k_verify_finalize", ("k_draft_stats", "k_verify_")))
+
+
 def read_counter(dirname, counter):
     """{dispatch id: (kernel name, summed value)} from a rocprofv3 counter_collection.csv"""
     import csv
@@ -228,28 +233,20 @@ def traffic_from(args):
         ids = sorted(c)
         # the calibration copy is the last large device-to-device copy before
         # the timed launches (the model set-up may copy earlier)
+        start, own = LAUNCH_KERNELS[args.workload == "verify"]
         copies = [i for i in ids if "copyBuffer" in c[i][0] and c[i][1] * 1024.0 >= CALIB_BYTES / 8]
-        if args.workload == "verify":
-            launches_all = [i for i in ids if "k_verify_rows" in c[i][0]]
-        else:
-            launches_all = [i for i in ids if "k_build_window" in c[i][0]]
-        copies = [i for i in copies if any(j > i for j in launches_all)]
+        copies = [i for i in copies if any(j > i and start in c[j][0] for j in ids)]
         if not copies:
             raise SystemExit(f"{counter}: no calibration copy found (run with --calibrate-copy)")
         cal = max(copies)
         fac = CALIB_BYTES / (c[cal][1] * 1024.0)
         facs[counter] = fac
+        starts = [i for i in ids if start in c[i][0] and i > cal]
         if args.workload == "verify":
-            launches = [i for i in ids if "k_verify_rows" in c[i][0] and i > cal]
-            tot = []
-            for i in launches:
-                fin = [j for j in ids if j > i and "k_verify_finalize" in c[j][0]]
-                tot.append(c[i][1] + (c[fin[0]][1] if fin else 0.0))
+            # whole launches follow each other: all of their kernels
+            tot = [sum(c[j][1] for j in ids if j > cal and any(k in c[j][0] for k in own)) / len(starts)]
         else:
-            starts = [i for i in ids if "k_build_window" in c[i][0] and i > cal]
-            tot = []
-            for a, b in zip(starts, starts[1:]):
-                tot.append(sum(c[j][1] for j in ids if a <= j < b))
+            tot = [sum(c[j][1] for j in ids if a <= j < b) for a, b in zip(starts, starts[1:])]
         if not tot:
             raise SystemExit(f"{counter}: no launches of the {args.workload} workload found")
         per[counter] = sum(tot) / len(tot) * 1024.0 * fac
