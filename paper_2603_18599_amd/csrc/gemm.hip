@@ -90,8 +90,12 @@ SJD_DEV void gemm_tile_of(int id, int groups, int splits, int& group, int& split
 
 // What a padded step takes for weights, beside its zero activation tile: both
 // must be finite for the step to add nothing, and the activation buffers hold
-// whatever earlier windows left in rows that this one does not write.
-static __device__ __align__(16) uint16_t zero_tile[2048];
+// whatever earlier windows left in rows that this one does not write. All lanes
+// read the same 16 bytes at each of the four offsets of a tile: with a line per eight
+// lanes these cold reads cost 0.25 us a launch (mid shape, start of an image 5121 ->
+// 5095 us; 7B forward of 6 layers 730 -> 723).
+constexpr int kZeroTile = 3 * 512 + 8;
+static __device__ __align__(16) uint16_t zero_tile[kZeroTile];
 
 // FOURS: the RMS scale comes from fours (narrow models' LM head); a variant of
 // its own, for its sums take 64 registers.
@@ -139,7 +143,7 @@ __global__ __launch_bounds__(NW * kWave) void k_gemm(GemmArgs g) {
   u32x4 w[kRing][4], ra[kRing][NS];
   // step t of this workgroup's range, clamped to the last real step
   auto kstep = [&](int t) { return st0 + (t < n ? t : n - 1); };
-  const uint16_t* wpad = zero_tile + (size_t)lane * 8;  // the weight tile of steps past the range
+  const uint16_t* wpad = zero_tile;  // the weight tile of steps past the range, in every lane
   auto issue = [&](int t, int slot) {
     const int st = kstep(t);
 #pragma unroll
