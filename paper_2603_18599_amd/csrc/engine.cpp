@@ -42,8 +42,8 @@ struct Ctx {
   const uint16_t* head = nullptr;
   std::vector<std::array<const uint16_t*, 9>> lw;
   std::vector<void*> owned;
-  // activations entering GEMMs are tiled hi / lo bf16 planes (forward.h); q is
-  // row-major, hi and lo planes
+  // activations entering GEMMs are tiled hi / lo bf16 planes (forward.h), one
+  // allocation that ends with the GEMM's zeros; q is row-major, hi and lo planes
   int mtiles = kPrefillRows / 32;  // Mpad / 32
   float* x = nullptr;
   uint16_t* xn = nullptr;
@@ -51,6 +51,7 @@ struct Ctx {
   uint16_t *q = nullptr, *q_lo = nullptr;
   uint16_t* att = nullptr;
   uint16_t* hbuf = nullptr;
+  const uint16_t* zeros = nullptr;  // kZeroTile of them
   uint16_t *kc = nullptr, *kc_lo = nullptr;
   uint16_t *vt = nullptr, *vt_lo = nullptr;
   // streams: one per image of a batch (up to four), two per image for a
@@ -220,8 +221,10 @@ int forward(Ctx& x, int M, const int32_t* prompt, const int32_t* n_dev, int n_ho
   // (prefill rows take the 64-row plan in windows of any length, so that a row's
   // summation order does not depend on its window)
   const Ctx::Plan* P = M > 64 && !prompt ? x.plan_wide : x.plan[M > 32 ? 1 : 0];
-  sjd::GemmArgs normed{};  // GEMM arguments that apply the RMSNorm row scale
-  normed.ncu = x.ncu;
+  sjd::GemmArgs plain{};
+  plain.ncu = x.ncu;
+  plain.zeros = x.zeros;
+  sjd::GemmArgs normed = plain;  // GEMM arguments that apply the RMSNorm row scale
   normed.ss = x.ss;
   normed.ss_n = sjd::norm_chunks(d);
   normed.inv_d = 1.0f / (float)d;
@@ -253,8 +256,8 @@ int forward(Ctx& x, int M, const int32_t* prompt, const int32_t* n_dev, int n_ho
           HIPTRY(sjd::launch_gemm_fused(sjd::kFusedResid, f, s));
           return SJD_OK;
         }
-        sjd::GemmArgs g{};
-        g.ncu = x.ncu; g.A = A; g.mtiles = mt; g.M = M; g.W = W; g.N = d; g.K = K; g.S = S; g.wide = wide;
+        sjd::GemmArgs g = plain;
+        g.A = A; g.mtiles = mt; g.M = M; g.W = W; g.N = d; g.K = K; g.S = S; g.wide = wide;
         g.out = x.rpart; g.plane = rplane; g.ldo = d;
         HIPTRY(sjd::launch_gemm(g, s));
         HIPTRY(sjd::launch_resid_norm(x.x, x.rpart, S, rplane, gain, M, d, x.xn, mt, nullptr, x.fours, s));
@@ -275,8 +278,8 @@ int forward(Ctx& x, int M, const int32_t* prompt, const int32_t* n_dev, int n_ho
     HIPTRY(sjd::launch_rope_kv(x.qkv, P[kProjQkv].S, qplane, x.win, n_dev, n_host, M, H, Hkv, hd, x.rope, kv, x.cap_pad,
                                sm, s));
     HIPTRY(sjd::launch_attention(a, hd, s));
-    g = sjd::GemmArgs{};
-    g.ncu = x.ncu; g.A = x.att; g.mtiles = mt; g.M = M; g.W = w[4]; g.N = d; g.K = Nq; g.S = P[kProjO].S;
+    g = plain;
+    g.A = x.att; g.mtiles = mt; g.M = M; g.W = w[4]; g.N = d; g.K = Nq; g.S = P[kProjO].S;
     g.wide = P[kProjO].wide; g.out = x.rpart; g.plane = rplane; g.ldo = d;
     HIPTRY(sjd::launch_gemm(g, s));
     HIPTRY(sjd::launch_resid_norm(x.x, x.rpart, P[kProjO].S, rplane, w[5], M, d, x.xn, mt, x.ss, nullptr, s));
@@ -285,8 +288,8 @@ int forward(Ctx& x, int M, const int32_t* prompt, const int32_t* n_dev, int n_ho
     g.wide = P[kProjGu].wide; g.out = x.gup; g.plane = guplane; g.ldo = 2 * F;
     HIPTRY(sjd::launch_gemm(g, s));
     HIPTRY(sjd::launch_swiglu(x.gup, P[kProjGu].S, guplane, M, F, x.hbuf, mt, s));
-    g = sjd::GemmArgs{};
-    g.ncu = x.ncu; g.A = x.hbuf; g.mtiles = mt; g.M = M; g.W = w[8]; g.N = d; g.K = F; g.S = P[kProjDown].S;
+    g = plain;
+    g.A = x.hbuf; g.mtiles = mt; g.M = M; g.W = w[8]; g.N = d; g.K = F; g.S = P[kProjDown].S;
     g.wide = P[kProjDown].wide; g.out = x.rpart; g.plane = rplane; g.ldo = d;
     HIPTRY(sjd::launch_gemm(g, s));
     pend = P[kProjDown].S;
@@ -396,7 +399,7 @@ Ctx::Plan tune_projection(Ctx& x, int proj, const std::vector<Ctx::Plan>& cand, 
     const auto& w = x.lw[rep % c.n_layers];
     const int S = pl.S;
     sjd::GemmArgs g{};
-    g.ncu = x.ncu; g.M = M; g.S = S; g.wide = pl.wide;
+    g.ncu = x.ncu; g.zeros = x.zeros; g.M = M; g.S = S; g.wide = pl.wide;
     if (proj == kProjQkv || proj == kProjGu) {
       g.ss = x.ss; g.ss_n = sjd::norm_chunks(d); g.inv_d = 1.0f / (float)d; g.eps = c.rms_eps;
       g.A = x.xn; g.mtiles = mt; g.K = d;
@@ -588,10 +591,10 @@ extern "C" int sjd_init(const sjd_config* cfg, const sjd_weights* w, void* strea
   const size_t kv = x.kv_elems * x.nstreams;  // every stream's caches
   const size_t xnsz = sjd::act_elems(d, x.mtiles), attsz = sjd::act_elems(Nq, x.mtiles),
                hsz = sjd::act_elems(F, x.mtiles);
-  if ((rc = dalloc(x, &x.x, (size_t)Mp * d)) || (rc = dalloc(x, &x.xn, xnsz)) ||
+  if ((rc = dalloc(x, &x.x, (size_t)Mp * d)) ||
+      (rc = dalloc(x, &x.xn, xnsz + attsz + hsz + sjd::kZeroTile)) ||
       (rc = dalloc(x, &x.q, (size_t)Mp * Nq)) ||
-      (rc = dalloc(x, &x.q_lo, (size_t)Mp * Nq)) || (rc = dalloc(x, &x.att, attsz)) ||
-      (rc = dalloc(x, &x.hbuf, hsz)) || (rc = dalloc(x, &x.kc, kv)) || (rc = dalloc(x, &x.kc_lo, kv)) ||
+      (rc = dalloc(x, &x.q_lo, (size_t)Mp * Nq)) || (rc = dalloc(x, &x.kc, kv)) || (rc = dalloc(x, &x.kc_lo, kv)) ||
       (rc = dalloc(x, &x.vt, kv)) || (rc = dalloc(x, &x.vt_lo, kv)) ||
       (rc = dalloc(x, &x.rope, (size_t)x.cap_pad * (hd / 2))) ||
       (rc = dalloc(x, &x.logits[0], (size_t)logit_rows(x) * c.V)) ||
@@ -602,6 +605,9 @@ extern "C" int sjd_init(const sjd_config* cfg, const sjd_weights* w, void* strea
       (rc = dalloc(x, &x.win, 1)) || (rc = dalloc(x, &x.rec, (size_t)x.B * c.L * sjd::kRecInts)) ||
       (rc = dalloc(x, &x.nonfinite, 16)))
     return fail(rc);
+  x.att = x.xn + xnsz;
+  x.hbuf = x.att + attsz;
+  x.zeros = x.hbuf + hsz;
   // split-K plan: the closed form aims for two to three workgroups per
   // compute unit; unless SJD_NO_TUNE, the process-wide tuned plan replaces it
   // (tuned below, by the first context that meets a shape)
@@ -711,11 +717,9 @@ extern "C" int sjd_init(const sjd_config* cfg, const sjd_weights* w, void* strea
   ok = ok && hipMemsetAsync(x.win, 0, sizeof(sjd::Window), s) == hipSuccess;
   ok = ok && hipMemsetAsync(x.x, 0, (size_t)Mp * d * sizeof(float), s) == hipSuccess;
   for (void* p : zero) ok = ok && hipMemsetAsync(p, 0, kv * 2, s) == hipSuccess;
-  ok = ok && hipMemsetAsync(x.xn, 0, xnsz * 2, s) == hipSuccess;
-  ok = ok && hipMemsetAsync(x.att, 0, attsz * 2, s) == hipSuccess;
+  ok = ok && hipMemsetAsync(x.xn, 0, (xnsz + attsz + hsz + sjd::kZeroTile) * 2, s) == hipSuccess;
   void* zero5[] = {x.q, x.q_lo};
   for (void* p : zero5) ok = ok && hipMemsetAsync(p, 0, (size_t)Mp * Nq * 2, s) == hipSuccess;
-  ok = ok && hipMemsetAsync(x.hbuf, 0, hsz * 2, s) == hipSuccess;
   if (!ok) return fail(SJD_EHIP);
   // rotary table in double precision: rope[pos][i] = (cos, sin)(pos * theta^(-2i/hd))
   {

@@ -58,7 +58,17 @@ struct GemmArgs {
   // result.)
   int wide;
   int ncu;  // the device's compute units
+  // What padded k-steps take for weights, beside their zero activation tile: both
+  // must be finite for such a step to add nothing, and the activation buffers hold
+  // whatever earlier windows left in rows that this one does not write.
+  const uint16_t* zeros;
 };
+// All lanes read the same 16 bytes at each of a tile's four offsets, and the zeros lie
+// behind the activations, in pages that the kernel reads anyway. A whole tile of them
+// in the library's own data cost 0.25 us a launch (mid shape, start of an image, us:
+// 5134, four lines of it 5096; with 48-slot windows, 6 layers: 2111, behind the
+// activations 2105; 7B forward of 6 layers 733, four lines 723).
+constexpr int kZeroTile = 3 * 512 + 8;
 
 // splits for about target_wgs workgroups of 4 (or, wide, 8) column blocks
 int gemm_splits(int N, int K, int target_wgs, bool wide);

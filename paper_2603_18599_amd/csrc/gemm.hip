@@ -88,15 +88,6 @@ SJD_DEV void gemm_tile_of(int id, int groups, int splits, int& group, int& split
   group = lin % groups;
 }
 
-// What a padded step takes for weights, beside its zero activation tile: both
-// must be finite for the step to add nothing, and the activation buffers hold
-// whatever earlier windows left in rows that this one does not write. All lanes
-// read the same 16 bytes at each of the four offsets of a tile: with a line per eight
-// lanes these cold reads cost 0.25 us a launch (mid shape, start of an image 5121 ->
-// 5095 us; 7B forward of 6 layers 730 -> 723).
-constexpr int kZeroTile = 3 * 512 + 8;
-static __device__ __align__(16) uint16_t zero_tile[kZeroTile];
-
 // FOURS: the RMS scale comes from fours (narrow models' LM head); a variant of
 // its own, for its sums take 64 registers.
 template <int kRing, int MT, int NW, bool FOURS = false>
@@ -143,7 +134,7 @@ __global__ __launch_bounds__(NW * kWave) void k_gemm(GemmArgs g) {
   u32x4 w[kRing][4], ra[kRing][NS];
   // step t of this workgroup's range, clamped to the last real step
   auto kstep = [&](int t) { return st0 + (t < n ? t : n - 1); };
-  const uint16_t* wpad = zero_tile;  // the weight tile of steps past the range, in every lane
+  const uint16_t* wpad = g.zeros;  // the weight tile of steps past the range, in every lane
   auto issue = [&](int t, int slot) {
     const int st = kstep(t);
 #pragma unroll
@@ -256,7 +247,7 @@ int gemm_splits(int N, int K, int target_wgs, bool wide) {
 
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
   if (g.M < 1 || g.M > 128 || g.M > 32 * g.mtiles || g.N % 32 || g.K % 64 || g.S < 1 || g.S > kGemmMaxSplits ||
-      g.ncu < 1)
+      g.ncu < 1 || !g.zeros)
     return hipErrorInvalidValue;
   const int MT = (g.M + 31) / 32;
   if (g.fours && (g.ss || g.ss_n > kFusedMaxChunks)) return hipErrorInvalidValue;
