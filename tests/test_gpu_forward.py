@@ -32,14 +32,14 @@ CASES = [
     ("7b", {"n_layers": 2, "n_prompt": 1240}),
     ("8b", {"n_layers": 1, "n_prompt": 4159}),
     # windows of up to 64 slots: two 32-row GEMM tiles, two attention slot
-    # halves; prompts longer than one 64-token prefill window
+    # halves; prompts of more than 64 tokens, two parts of a prefill window
     ("tiny", {"L": 64, "n_prompt": 100}),
     ("7b", {"n_layers": 2, "L": 64, "n_prompt": 70}),
     ("8b", {"n_layers": 2, "L": 48, "n_prompt": 40}),
     # 128-dim heads over long caches: the split-KV attention with many
     # 128-key chunks and their combine (the 7B benchmark step takes 10 chunks
-    # per head at 1239 cached rows; prefill windows of 64 rows take two slot
-    # halves), on narrow bf16 models so that the oracle's prefill stays quick
+    # per head at 1239 cached rows; prefill windows of 128 rows take four slot
+    # blocks), on narrow bf16 models so that the oracle's prefill stays quick
     ("tiny", {"n_layers": 1, "d_model": 512, "n_heads": 4, "n_kv_heads": 4, "head_dim": 128, "ffn_dim": 1024,
               "n_prompt": 1271, "L": 32, "weights_f32": False}),
     ("tiny", {"n_layers": 2, "d_model": 512, "n_heads": 4, "n_kv_heads": 2, "head_dim": 128, "ffn_dim": 1024,
